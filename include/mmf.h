@@ -133,11 +133,14 @@ int mmf_act_quant_ex(const void *x, int x_is_f32, const float *gamma, int8_t *q,
  *   y[m][n] = a_scale[m] * w_scale * sum_k q[m][k] t[n][k]
  * with q, a_scale from the act-quant step above and t from Wpacked.  The
  * integer sum is exact; the product is fp32 (a_scale[m] * w_scale first).
- * Up to 32 tokens (K <= 2048) or 64 (larger K) take the decode kernel in
- * launches of at most 16 tokens (16x16x64 int8 MFMA over 16 columns by the
- * token rows; weights streamed once per launch), larger M the int8 MFMA GEMM
- * kernel.  Allocates its M*K + 8*M byte scratch stream-ordered
- * (hipMallocAsync); mmf_bitlinear_fwd_ws takes caller scratch instead.
+ * Up to 16 tokens take the fused decode kernel (one launch; 16x16x64 int8
+ * MFMA over 16 columns by the token rows), a few hundred act-quant and the
+ * int8 MFMA kernel that splits K over the waves of a workgroup, larger M
+ * act-quant and the tiled int8 MFMA GEMM kernel; all give the same bits.
+ * Allocates its M*K + 8*M byte scratch stream-ordered (hipMallocAsync) beyond
+ * the fused decode kernel; under stream capture, up to 32 tokens (K <= 2048)
+ * or 64 (larger K) run as decode launches of 16 tokens, which need none.
+ * mmf_bitlinear_fwd_ws takes caller scratch instead.
  * x: [M][K] bf16 bits; gamma: [K] or NULL; Wpacked: [K/16][N]; w_scale: [1];
  * y: [M][N] float32 out.
  */
@@ -236,10 +239,8 @@ int mmf_ternary_gemm_i32(const int8_t *q, const uint32_t *Wpacked,
  *
  * mmf_glu_fwd: x [M][K] bf16 bits (mmf_glu_fwd_f32: float32); gamma [K] or
  * NULL; Wgu_packed [K/16][2L] from mmf_glu_pack; w_scales [2] = gate, up;
- * p [M][L] float32 out.  Up to 32 tokens (K <= 2048) or 64 (larger K) run
- * the fused decode kernel with the same SiLU(g) * u epilogue (launches of at
- * most 16 tokens; the result is bit-identical to the GEMM kernel's), larger M
- * the int8 MFMA GEMM kernel.  Allocates the
+ * p [M][L] float32 out.  The kernels of mmf_bitlinear_fwd with the SiLU(g) * u
+ * epilogue (the same bits from each).  Allocates the
  * same stream-ordered scratch as mmf_bitlinear_fwd; mmf_glu_fwd_ws takes
  * caller scratch of mmf_bitlinear_workspace_bytes(M, K) bytes instead.
  */
@@ -256,7 +257,7 @@ int mmf_glu_fwd_ws(const void *x, int x_is_f32, const float *gamma,
                    int64_t M, int64_t K, int64_t L, void *workspace,
                    size_t workspace_bytes, hipStream_t stream);
 /* The contraction stage of mmf_glu_fwd on its own, from quantised
- * activations (q, a_scale, q_rowsum as written by mmf_act_quant); always the
+ * activations (q, a_scale, q_rowsum as written by mmf_act_quant); always an
  * int8 MFMA kernel.  Allocates nothing. */
 int mmf_ternary_gemm_glu(const int8_t *q, const float *a_scale, const int32_t *q_rowsum,
                          const uint32_t *Wgu_packed, const float *w_scales, float *p,
@@ -309,8 +310,7 @@ int mmf_bitlinear_fwd_bias(const void *x, int x_is_f32, const float *gamma,
  * with s evaluated as for the GLU gate (hardware exp2 and reciprocal). The
  * recurrence's output gate o' = g * s(h) uses the same s.
  * x [M][K] bf16 bits or float32 (x_is_f32); bias [3d] or NULL; lb [d] or
- * NULL.  M <= 32 (K <= 2048) or 64 (larger K) runs the fused decode kernel
- * (launches of at most 16 tokens), larger M the int8 MFMA GEMM kernel. */
+ * NULL.  The kernels of mmf_bitlinear_fwd with the affine epilogue. */
 size_t mmf_mlgru_proj_workspace_bytes(int64_t M, int64_t K, int64_t d);
 int mmf_mlgru_proj(const void *x, int x_is_f32, const float *gamma, const uint32_t *Wfcg,
                    const float *w_scales, const float *bias, const float *lb, float *fcg,
@@ -318,7 +318,7 @@ int mmf_mlgru_proj(const void *x, int x_is_f32, const float *gamma, const uint32
                    hipStream_t stream);
 
 /* The contraction stage of mmf_mlgru_proj on its own, from quantised
- * activations (q, a_scale, q_rowsum as written by mmf_act_quant); always the
+ * activations (q, a_scale, q_rowsum as written by mmf_act_quant); always an
  * int8 MFMA kernel.  Allocates nothing. */
 int mmf_mlgru_proj_q(const int8_t *q, const float *a_scale, const int32_t *q_rowsum,
                      const uint32_t *Wfcg, const float *w_scales, const float *bias,
@@ -401,10 +401,9 @@ int mmf_bitlinear_bwd(const uint16_t *dO, const void *x, int x_is_f32, const flo
                       void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 /*
- * Kernel selection for the contraction: MMF_PATH_AUTO (decode kernel for
- * M <= 32 at K <= 2048 and M <= 64 beyond, in launches of at most 16
- * tokens; the GEMM kernel otherwise),
- * MMF_PATH_GEMV or MMF_PATH_GEMM force one kernel for every M (the decode
+ * Kernel selection for the contraction: MMF_PATH_AUTO (the fused decode
+ * kernel for M <= 16, the K-split kernel for a few hundred rows, the tiled
+ * GEMM kernel otherwise; see mmf_bitlinear_fwd), MMF_PATH_GEMV or MMF_PATH_GEMM force one kernel for every M (the decode
  * kernel handles at most 16 tokens per launch and is launched once per
  * 16-token slice when forced).  Process-wide; returns
  * the previous setting, or -MMF_ERR_ARG for an unknown value.
@@ -415,8 +414,8 @@ int mmf_bitlinear_bwd(const uint16_t *dO, const void *x, int x_is_f32, const flo
 int mmf_set_path(int path);
 
 /*
- * The workgroup tile of the prefill (MFMA) contraction for an M x K x N
- * problem on `cus` compute units, as the library plans it for its launches
+ * The workgroup tile of the tiled prefill (MFMA GEMM) contraction for an
+ * M x K x N problem on `cus` compute units, as the library plans it for its launches
  * (host only: no device call, nothing enqueued; for problems split into row
  * slices by the 32-bit offset limit, the first slice's plan).  For callers
  * sizing their own work and for tests that must know which kernel form a

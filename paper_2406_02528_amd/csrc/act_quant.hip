@@ -63,7 +63,7 @@ template <typename XT, int W, int VPL>
 __global__ __launch_bounds__(256) void act_quant_kernel(
     const XT* __restrict__ x, const float* __restrict__ gamma,
     int8_t* __restrict__ q, float* __restrict__ a_scale,
-    int32_t* __restrict__ q_rowsum, float* __restrict__ rstd, int64_t M, int K) {
+    int32_t* __restrict__ q_rowsum, float* __restrict__ rstd, int64_t M, int K, bool tiled) {
   using V = Vec<XT>;
   constexpr int E = V::kElems;
   constexpr int kRows = kRowsPerBlock / W;  // rows per block
@@ -122,7 +122,16 @@ __global__ __launch_bounds__(256) void act_quant_kernel(
   const int64_t srow = live ? row : 0;
   const int nvec = K / E;
   const typename V::Raw* xr = reinterpret_cast<const typename V::Raw*>(x + srow * K);
-  int8_t* qr = q + srow * K;
+  // where a vector of E values starting at feature k goes (pieces of 64 bytes
+  // hold whole vectors)
+  const int64_t t16 = srow / 16 * 16;
+  const int trows = static_cast<int>(M - t16 < 16 ? M - t16 : 16);
+  int8_t* const qr = q + (tiled ? t16 : srow) * K;
+  auto q_at = [&](int k) -> int8_t* {
+    if (!tiled) return qr + k;  // uniform
+    const int s = k / 64, piece = K - 64 * s < 64 ? K - 64 * s : 64;
+    return qr + static_cast<int64_t>(64 * s) * trows + static_cast<int>(srow - t16) * piece + k % 64;
+  };
 
   if constexpr (VPL > 0) {
     // Every load of the row and of gamma is issued at once, without branches:
@@ -183,7 +192,7 @@ __global__ __launch_bounds__(256) void act_quant_kernel(
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
       const int v = rl + W * kWave * i;
-      if (live && v < nvec) quantise_store<E>(qr + v * E, xf[i], s, rs);
+      if (live && v < nvec) quantise_store<E>(q_at(v * E), xf[i], s, rs);
     }
     rs = combine_i32(wave_sum_i32(rs));
     if (live && rl == 0) {
@@ -231,7 +240,7 @@ __global__ __launch_bounds__(256) void act_quant_kernel(
           f[e] = f[e] * r;
           if (gamma != nullptr) f[e] = f[e] * gamma[v * E + e];
         }
-        quantise_store<E>(qr + v * E, f, s, rs);
+        quantise_store<E>(q_at(v * E), f, s, rs);
       }
     }
     rs = combine_i32(wave_sum_i32(rs));
@@ -250,13 +259,13 @@ __global__ __launch_bounds__(256) void act_quant_kernel(
 // past the row's end return zeros but cost nearly a real load each).
 template <typename XT, int W>
 hipError_t launch_w(const XT* x, const float* gamma, int8_t* q, float* a_scale, int32_t* q_rowsum,
-                    float* rstd, int64_t M, int K, int vpl, hipStream_t stream) {
+                    float* rstd, int64_t M, int K, bool tiled, int vpl, hipStream_t stream) {
   constexpr int kRows = kRowsPerBlock / W;
   const dim3 grid(static_cast<unsigned>((M + kRows - 1) / kRows));
   const dim3 block(kWave * kRowsPerBlock);
 #define MMF_AQ_LAUNCH(V)                                                             \
   hipLaunchKernelGGL((act_quant_kernel<XT, W, V>), grid, block, 0, stream, x, gamma, \
-                     q, a_scale, q_rowsum, rstd, M, K)
+                     q, a_scale, q_rowsum, rstd, M, K, tiled)
   switch (vpl) {
     case 1: MMF_AQ_LAUNCH(1); break;
     case 2: MMF_AQ_LAUNCH(2); break;
@@ -272,27 +281,27 @@ hipError_t launch_w(const XT* x, const float* gamma, int8_t* q, float* a_scale, 
 
 template <typename XT>
 hipError_t launch_typed(const XT* x, const float* gamma, int8_t* q, float* a_scale,
-                        int32_t* q_rowsum, float* rstd, int64_t M, int K, hipStream_t stream) {
+                        int32_t* q_rowsum, float* rstd, int64_t M, int K, bool tiled, hipStream_t stream) {
   constexpr int E = Vec<XT>::kElems;
   const int nvec = K / E;
   if (nvec <= kWave * 4)
-    return launch_w<XT, 1>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, (nvec + kWave - 1) / kWave, stream);
+    return launch_w<XT, 1>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, tiled, (nvec + kWave - 1) / kWave, stream);
   if (nvec <= 2 * kWave * 4)
-    return launch_w<XT, 2>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, (nvec + 2 * kWave - 1) / (2 * kWave),
+    return launch_w<XT, 2>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, tiled, (nvec + 2 * kWave - 1) / (2 * kWave),
                            stream);
   const int vpl = (nvec + 4 * kWave - 1) / (4 * kWave);
-  return launch_w<XT, 4>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, vpl <= 8 ? vpl : 0, stream);
+  return launch_w<XT, 4>(x, gamma, q, a_scale, q_rowsum, rstd, M, K, tiled, vpl <= 8 ? vpl : 0, stream);
 }
 
 }  // namespace
 
 hipError_t launch_act_quant(const void* x, bool x_is_f32, const float* gamma, int8_t* q,
                             float* a_scale, int32_t* q_rowsum, int64_t M, int K,
-                            hipStream_t stream, float* rstd) {
+                            hipStream_t stream, float* rstd, bool tiled) {
   if (M == 0) return hipSuccess;
   if (x_is_f32)
-    return launch_typed(static_cast<const float*>(x), gamma, q, a_scale, q_rowsum, rstd, M, K, stream);
-  return launch_typed(static_cast<const uint16_t*>(x), gamma, q, a_scale, q_rowsum, rstd, M, K, stream);
+    return launch_typed(static_cast<const float*>(x), gamma, q, a_scale, q_rowsum, rstd, M, K, tiled, stream);
+  return launch_typed(static_cast<const uint16_t*>(x), gamma, q, a_scale, q_rowsum, rstd, M, K, tiled, stream);
 }
 
 }  // namespace mmf

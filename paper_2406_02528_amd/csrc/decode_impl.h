@@ -59,15 +59,6 @@ constexpr int vec_elems() { return (S == Src::kF32 || S == Src::kMlgru) ? 4 : 8;
 // group size measured 0.4-0.5 us slower per one-token launch).
 constexpr int row_waves_for(int mt) { return mt <= 4 ? 4 : mt <= 8 ? 2 : 1; }
 
-// Barrier for LDS traffic only: the fences are restricted to the local
-// address space, so the barrier waits for this wave's LDS operations but not
-// for its global loads in flight (a plain __syncthreads would wait for them).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 struct Shared {
   int8_t* q;        // [mt][q_stride]
   int q_stride;     // bytes from one token row of q to the next

@@ -599,6 +599,15 @@ int gemm_tile_choice(int64_t rows, int64_t N, int cus) {
   return best;
 }
 
+double gemm_alone_us(int64_t rows, int K, int64_t N, int cus) {
+  struct Shape { int64_t bm, bn; double us, us_per_k; };
+  constexpr Shape kShapes[] = {
+      {128, 512, 3.2, 0.0099}, {64, 512, 3.2, 0.0066}, {64, 256, 3.2, 0.0038}, {256, 256, 8.0, 0.0125}};
+  const Shape& s = kShapes[N % 4 != 0 ? 3 : gemm_tile_choice(rows, N, cus)];
+  const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), c = cus > 0 ? cus : 256;
+  return static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K);
+}
+
 int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus) {
   if (N % 4 != 0) return kPlan256x256;
   const int choice = gemm_tile_choice(rows, N, cus);

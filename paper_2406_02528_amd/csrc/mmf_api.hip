@@ -66,9 +66,34 @@ bool use_decode(int64_t M, int64_t K, int64_t N, bool from_x, bool x_is_f32) {
                           x_is_f32);
 }
 
-// Contraction from quantised activations.  Decode-sized slices of at most 16
-// tokens keep q in LDS when it fits, else read it from global memory.
+// Whether the automatic path contracts these rows with K split over the waves
+// of a workgroup (skinny.hip).
+bool use_skinny(int64_t M, int64_t K, int64_t N, mmf::Epilogue ep, bool tiled) {
+  return g_path.load(std::memory_order_relaxed) == MMF_PATH_AUTO &&
+         mmf::skinny_takes(M, static_cast<int>(K), N, ep, tiled, mmf::device_cus());
+}
+
+// Whether the decode kernel contracts these rows of q in one launch (its
+// dequantising and raw epilogues only).
+bool one_decode_launch(int64_t M, int64_t K, int64_t N, mmf::Epilogue ep) {
+  return (ep == mmf::Epilogue::kDequantF32 || ep == mmf::Epilogue::kRawI32) && M <= kDecodeMaxTokens &&
+         mmf::decode_fits(M, static_cast<int>(K), N, false, false);
+}
+
+// The MFMA contraction from rows of q: the K-split kernel for few rows, else
+// the tiled GEMM kernel.
+hipError_t contract_mfma(const mmf::ContractArgs& a, hipStream_t stream) {
+  if (use_skinny(a.M, a.K, a.N, a.epilogue, false)) return mmf::launch_skinny(a, false, stream);
+  return mmf::launch_gemm(a, stream);
+}
+
+// Contraction from quantised activations.  Up to 16 tokens keep q in LDS when
+// it fits; more take the MFMA kernels.  On the forced decode path every slice
+// of 16 tokens runs as a decode launch, those whose q does not fit LDS reading
+// it from global memory.
 hipError_t contract(const mmf::ContractArgs& a, hipStream_t stream) {
+  if (!one_decode_launch(a.M, a.K, a.N, a.epilogue) && use_skinny(a.M, a.K, a.N, a.epilogue, false))
+    return mmf::launch_skinny(a, false, stream);
   if (!use_decode(a.M, a.K, a.N, false, false)) return mmf::launch_gemm(a, stream);
   for (int64_t m0 = 0; m0 < a.M; m0 += kDecodeMaxTokens) {
     const int64_t mt = a.M - m0 < kDecodeMaxTokens ? a.M - m0 : kDecodeMaxTokens;
@@ -97,6 +122,48 @@ bool fused_decode(int64_t M, int64_t K, int64_t N, bool x_is_f32) {
   if (!use_decode(M, K, N, true, x_is_f32)) return false;
   const int64_t mt = M < kDecodeMaxTokens ? M : kDecodeMaxTokens;
   return mmf::decode_fits(mt, static_cast<int>(K), N, true, x_is_f32);
+}
+
+// Whether a forward from x runs as act-quant (q tiled, into scratch) and the
+// K-split contraction although fused decode launches would take it: one fused
+// launch up to 16 tokens, but its row stage repeats in every workgroup and
+// each further 16 tokens stream the weights again.  Measured forward calls
+// from bf16 x, fused slices -> act-quant + K-split: see skinny_takes.
+bool prefers_skinny(int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep) {
+  return (M > kDecodeMaxTokens || !fused_decode(M, K, N, x_is_f32)) && use_skinny(M, K, N, ep, true);
+}
+
+// Whether work on `stream` is being captured into a graph (or that cannot be
+// told): calls that would only now need scratch then keep the fused decode
+// launches, which allocate nothing.
+bool capturing(hipStream_t stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// Scratch a forward without caller workspace allocates: none when it runs as
+// fused decode launches.
+size_t fwd_need(int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep, hipStream_t stream) {
+  if (fused_decode(M, K, N, x_is_f32) && (!prefers_skinny(M, K, N, x_is_f32, ep) || capturing(stream))) return 0;
+  return fwd_scratch(M, K).total;
+}
+
+// act-quant into `scratch` and the contraction behind it: tiled q and the
+// K-split kernel for few rows, rows of q and `contract_rows` otherwise.
+template <class C>
+hipError_t quant_contract(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
+                          const float* w_scales, void* out, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep,
+                          const mmf::Affine& aff, char* scratch, hipStream_t stream, C&& contract_rows) {
+  const FwdScratch s = fwd_scratch(M, K);
+  int8_t* q = reinterpret_cast<int8_t*>(scratch + s.q_off);
+  float* a_scale = reinterpret_cast<float*>(scratch + s.a_off);
+  int32_t* rowsum = reinterpret_cast<int32_t*>(scratch + s.r_off);
+  const bool tiled = !one_decode_launch(M, K, N, ep) && use_skinny(M, K, N, ep, true);
+  const hipError_t e = mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M, static_cast<int>(K), stream,
+                                             nullptr, tiled);
+  if (e != hipSuccess) return e;
+  const mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scales, out, M, static_cast<int>(K), N, ep, aff};
+  return tiled ? mmf::launch_skinny(a, true, stream) : contract_rows(a, stream);
 }
 
 // Shape limits of the kernels a call will run, checked before anything is
@@ -146,52 +213,14 @@ int check_fwd(const void* x, bool x_is_f32, const float* gamma, const uint32_t* 
   return MMF_OK;
 }
 
+// `scratch` may be nullptr when fwd_need is 0.
 int run_fwd(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
             const float* w_scale, float* y, int64_t M, int64_t K, int64_t N, char* scratch,
             hipStream_t stream) {
-  if (fused_decode(M, K, N, x_is_f32))
+  const mmf::Epilogue ep = mmf::Epilogue::kDequantF32;
+  if (fused_decode(M, K, N, x_is_f32) && (scratch == nullptr || !prefers_skinny(M, K, N, x_is_f32, ep)))
     return hip_status(run_fused_decode(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, stream));
-  const FwdScratch s = fwd_scratch(M, K);
-  int8_t* q = reinterpret_cast<int8_t*>(scratch + s.q_off);
-  float* a_scale = reinterpret_cast<float*>(scratch + s.a_off);
-  int32_t* rowsum = reinterpret_cast<int32_t*>(scratch + s.r_off);
-  hipError_t e = mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M,
-                                       static_cast<int>(K), stream);
-  if (e != hipSuccess) return MMF_ERR_HIP;
-  mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scale, y, M, static_cast<int>(K), N,
-                      mmf::Epilogue::kDequantF32};
-  return hip_status(contract(a, stream));
-}
-
-int fwd_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
-              const float* w_scale, float* y, int64_t M, int64_t K, int64_t N,
-              hipStream_t stream) {
-  if (int st = check_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
-  if (M == 0 || N == 0) return MMF_OK;
-  if (fused_decode(M, K, N, x_is_f32))
-    return hip_status(run_fused_decode(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, stream));
-  const FwdScratch s = fwd_scratch(M, K);
-  void* scratch = nullptr;
-  if (hipMallocAsync(&scratch, s.total, stream) != hipSuccess) return MMF_ERR_HIP;
-  const int st = run_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N,
-                         static_cast<char*>(scratch), stream);
-  const hipError_t fe = hipFreeAsync(scratch, stream);
-  if (st != MMF_OK) return st;
-  return hip_status(fe);
-}
-
-int act_quant_common(const void* x, int x_is_f32, const float* gamma, int8_t* q,
-                     float* a_scale, int32_t* q_rowsum, int64_t M, int64_t K,
-                     hipStream_t stream) {
-  if (int st = check_dtype(x_is_f32)) return st;
-  if (int st = check_shape(M, K, 0)) return st;
-  if (M == 0) return MMF_OK;
-  if (!x || !q || !a_scale) return MMF_ERR_NULL;
-  if (!aligned16(x) || !aligned16(q) || !aligned16(a_scale) || (gamma && !aligned16(gamma)) ||
-      (q_rowsum && !aligned16(q_rowsum)))
-    return MMF_ERR_ALIGN;
-  return hip_status(mmf::launch_act_quant(x, x_is_f32 == 1, gamma, q, a_scale, q_rowsum, M,
-                                          static_cast<int>(K), stream));
+  return hip_status(quant_contract(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, ep, {}, scratch, stream, contract));
 }
 
 // Runs `run(scratch)` on the caller's workspace (checked against `need`), or
@@ -212,6 +241,31 @@ int with_workspace(void* workspace, size_t workspace_bytes, size_t need, hipStre
   return hip_status(fe);
 }
 
+int fwd_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
+              const float* w_scale, float* y, int64_t M, int64_t K, int64_t N,
+              hipStream_t stream) {
+  if (int st = check_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
+  if (M == 0 || N == 0) return MMF_OK;
+  const size_t need = fwd_need(M, K, N, x_is_f32, mmf::Epilogue::kDequantF32, stream);
+  return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
+    return run_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, scratch, stream);
+  });
+}
+
+int act_quant_common(const void* x, int x_is_f32, const float* gamma, int8_t* q,
+                     float* a_scale, int32_t* q_rowsum, int64_t M, int64_t K,
+                     hipStream_t stream) {
+  if (int st = check_dtype(x_is_f32)) return st;
+  if (int st = check_shape(M, K, 0)) return st;
+  if (M == 0) return MMF_OK;
+  if (!x || !q || !a_scale) return MMF_ERR_NULL;
+  if (!aligned16(x) || !aligned16(q) || !aligned16(a_scale) || (gamma && !aligned16(gamma)) ||
+      (q_rowsum && !aligned16(q_rowsum)))
+    return MMF_ERR_ALIGN;
+  return hip_status(mmf::launch_act_quant(x, x_is_f32 == 1, gamma, q, a_scale, q_rowsum, M,
+                                          static_cast<int>(K), stream));
+}
+
 // GLU (gated up-projection): x -> RMSNorm + quantisation -> the interleaved
 // gate/up contraction with the SiLU(g) * u epilogue: fused decode launches for
 // the token counts the decode kernel takes, the MFMA kernel otherwise.
@@ -230,8 +284,10 @@ int check_glu(const void* x, bool x_is_f32, const float* gamma, const uint32_t* 
 int run_glu(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
             const float* w_scales, float* p, int64_t M, int64_t K, int64_t L, char* scratch,
             hipStream_t stream) {
+  const mmf::Epilogue ep = mmf::Epilogue::kGluF32;
   // few tokens: fused decode launches with the GLU epilogue (no scratch)
-  if (fused_decode(M, K, 2 * L, x_is_f32)) {
+  if (fused_decode(M, K, 2 * L, x_is_f32) &&
+      (scratch == nullptr || !prefers_skinny(M, K, 2 * L, x_is_f32, ep))) {
     const size_t xsz = x_is_f32 ? 4 : 2;
     for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
       const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
@@ -242,16 +298,8 @@ int run_glu(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wg
     }
     return MMF_OK;
   }
-  const FwdScratch s = fwd_scratch(M, K);
-  int8_t* q = reinterpret_cast<int8_t*>(scratch + s.q_off);
-  float* a_scale = reinterpret_cast<float*>(scratch + s.a_off);
-  int32_t* rowsum = reinterpret_cast<int32_t*>(scratch + s.r_off);
-  hipError_t e = mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M,
-                                       static_cast<int>(K), stream);
-  if (e != hipSuccess) return MMF_ERR_HIP;
-  mmf::ContractArgs a{q, a_scale, rowsum, Wgu, w_scales, p, M, static_cast<int>(K), 2 * L,
-                      mmf::Epilogue::kGluF32};
-  return hip_status(mmf::launch_gemm(a, stream));
+  return hip_status(quant_contract(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, 2 * L, ep, {}, scratch, stream,
+                                   contract_mfma));
 }
 
 int glu_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
@@ -259,8 +307,7 @@ int glu_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* 
               hipStream_t stream) {
   if (int st = check_glu(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, L)) return st;
   if (M == 0 || L == 0) return MMF_OK;
-  // the fused decode launches need no scratch
-  const size_t need = fused_decode(M, K, 2 * L, x_is_f32) ? 0 : fwd_scratch(M, K).total;
+  const size_t need = fwd_need(M, K, 2 * L, x_is_f32, mmf::Epilogue::kGluF32, stream);
   return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
     return run_glu(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, L, scratch, stream);
   });
@@ -268,33 +315,25 @@ int glu_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* 
 
 // ---- affine forward (bias and per-segment activations after the dequant) ----
 
-// Fused decode launches when every slice of at most 16 tokens fits the fused
-// kernel, else activation quantisation into `scratch` (fwd_scratch) and the
-// MFMA kernel for every M.
+// Fused decode launches for the token counts the fused kernel takes, else
+// activation quantisation into `scratch` (fwd_scratch) and the MFMA kernels.
 int run_affine(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
                const float* w_scales, const mmf::Affine& aff, float* y, int64_t M, int64_t K,
                int64_t N, char* scratch, hipStream_t stream) {
-  if (fused_decode(M, K, N, x_is_f32)) {
+  const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
+  if (fused_decode(M, K, N, x_is_f32) && (scratch == nullptr || !prefers_skinny(M, K, N, x_is_f32, ep))) {
     const size_t xsz = x_is_f32 ? 4 : 2;
     for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
       const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
       mmf::DecodeArgs d{static_cast<const char*>(x) + m0 * K * xsz, x_is_f32, gamma, nullptr,
                         nullptr, nullptr, Wpacked, w_scales, y + m0 * N, mt,
-                        static_cast<int>(K), N, mmf::Epilogue::kAffineF32, aff};
+                        static_cast<int>(K), N, ep, aff};
       if (mmf::launch_decode(d, stream) != hipSuccess) return MMF_ERR_HIP;
     }
     return MMF_OK;
   }
-  const FwdScratch s = fwd_scratch(M, K);
-  int8_t* q = reinterpret_cast<int8_t*>(scratch + s.q_off);
-  float* a_scale = reinterpret_cast<float*>(scratch + s.a_off);
-  int32_t* rowsum = reinterpret_cast<int32_t*>(scratch + s.r_off);
-  if (mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M, static_cast<int>(K), stream) !=
-      hipSuccess)
-    return MMF_ERR_HIP;
-  mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scales, y, M, static_cast<int>(K), N,
-                      mmf::Epilogue::kAffineF32, aff};
-  return hip_status(mmf::launch_gemm(a, stream));
+  return hip_status(quant_contract(x, x_is_f32, gamma, Wpacked, w_scales, y, M, K, N, ep, aff, scratch, stream,
+                                   contract_mfma));
 }
 
 bool aligned16_or_null(const void* p) { return p == nullptr || aligned16(p); }
@@ -644,7 +683,7 @@ int mmf_ternary_gemm_glu(const int8_t* q, const float* a_scale, const int32_t* q
     return MMF_ERR_ALIGN;
   mmf::ContractArgs a{q, a_scale, q_rowsum, Wgu_packed, w_scales, p, M, static_cast<int>(K), 2 * L,
                       mmf::Epilogue::kGluF32};
-  return hip_status(mmf::launch_gemm(a, stream));
+  return hip_status(contract_mfma(a, stream));
 }
 
 int mmf_bitlinear_fwd_bias(const void* x, int x_is_f32, const float* gamma,
@@ -660,7 +699,7 @@ int mmf_bitlinear_fwd_bias(const void* x, int x_is_f32, const float* gamma,
   aff.bias = bias;
   aff.seg = N;
   aff.acts = mmf::kActIdentity;
-  const size_t need = fused_decode(M, K, N, x_is_f32 == 1) ? 0 : fwd_scratch(M, K).total;
+  const size_t need = fwd_need(M, K, N, x_is_f32 == 1, mmf::Epilogue::kAffineF32, stream);
   return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
     return run_affine(x, x_is_f32 == 1, gamma, Wpacked, w_scale, aff, y, M, K, N, scratch, stream);
   });
@@ -708,7 +747,7 @@ int mmf_mlgru_proj_q(const int8_t* q, const float* a_scale, const int32_t* q_row
   aff.acts = kMlgruActs;
   mmf::ContractArgs a{q, a_scale, q_rowsum, Wfcg, w_scales, fcg, M, static_cast<int>(K), 3 * d,
                       mmf::Epilogue::kAffineF32, aff};
-  return hip_status(mmf::launch_gemm(a, stream));
+  return hip_status(contract_mfma(a, stream));
 }
 
 size_t mmf_mlgru_scan_workspace_bytes(int64_t B, int64_t T, int64_t d) {
@@ -770,7 +809,8 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
     // array: the recurrence and output gate run in the output projection's
     // prologue (no launch, no o' round trip).  Identical arithmetic to the
     // separate kernels, so identical results.
-    if (T == 1 && (h_last == nullptr || h_last != h0) && fused_decode(M, d, d, true)) {
+    if (T == 1 && (h_last == nullptr || h_last != h0) && fused_decode(M, d, d, true) &&
+        !prefers_skinny(M, d, d, true, mmf::Epilogue::kAffineF32)) {
       for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
         const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
         mmf::DecodeArgs a{fcg + m0 * 3 * d, true, gamma_o, nullptr, nullptr, nullptr, Wo, w_scale_o,
@@ -821,7 +861,7 @@ int mmf_bitlinear_train_fwd(const void* x, int x_is_f32, const float* gamma, con
     aff.acts = mmf::kActIdentity;
     mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scale, y, M, static_cast<int>(K), N,
                         bias ? mmf::Epilogue::kAffineF32 : mmf::Epilogue::kDequantF32, aff};
-    return hip_status(mmf::launch_gemm(a, stream));
+    return hip_status(contract_mfma(a, stream));
   });
 }
 

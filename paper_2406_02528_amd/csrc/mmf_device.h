@@ -88,6 +88,15 @@ __device__ __forceinline__ int wave_sum_i32(int v) {
          (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
 }
 
+// Barrier for LDS traffic only: the fences are restricted to the local
+// address space, so the barrier waits for this wave's LDS operations but not
+// for its global loads in flight (a plain __syncthreads would wait for them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---------------------------------------------------------------------------
 // RMSNorm reciprocal scale r = 1 / sqrt(sum_k x_k^2 / K + eps), eps = 1e-6,
 // returned in fp32 and equal to the fp32 rounding of the fp64 sequence

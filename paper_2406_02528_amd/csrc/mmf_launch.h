@@ -6,11 +6,23 @@
 
 namespace mmf {
 
+// The TiledQ layout of q (M * K bytes, as the rows): row blocks of 16 rows at
+// 16 b K; in a block of mr rows (16, or M % 16 in the last) the 64-byte pieces
+// of step s = k / 64 at 64 s mr, row r's at 64 r within them (K % 64 bytes per
+// row in a last step of less than 64).  Byte offset of row m, feature k:
+__host__ __device__ inline int64_t tiled_q_offset(int64_t m, int k, int64_t M, int K) {
+  const int64_t b = m / 16, r = m % 16;
+  const int64_t mr = M - 16 * b < 16 ? M - 16 * b : 16;
+  const int s = k / 64, piece = K - 64 * s < 64 ? K - 64 * s : 64;
+  return 16 * b * K + 64 * s * mr + r * piece + k % 64;
+}
+
 // RMSNorm + absmax int8 quantisation of M rows of K features (K % 16 == 0);
-// rstd (optional) receives each row's 1/sqrt(mean x^2 + eps).
+// rstd (optional) receives each row's 1/sqrt(mean x^2 + eps); `tiled` writes q
+// in the TiledQ layout instead of rows.
 hipError_t launch_act_quant(const void* x, bool x_is_f32, const float* gamma, int8_t* q,
                             float* a_scale, int32_t* q_rowsum, int64_t M, int K,
-                            hipStream_t stream, float* rstd = nullptr);
+                            hipStream_t stream, float* rstd = nullptr, bool tiled = false);
 
 // q_rowsum[m] = sum_k q[m][k].
 hipError_t launch_row_sum(const int8_t* q, int32_t* q_rowsum, int64_t M, int K,
@@ -107,6 +119,9 @@ int gemm_tile_choice(int64_t rows, int64_t N, int cus);
 // epilogue `ep` on `cus` compute units (the values of MMF_TILE_* in mmf.h).
 enum GemmPlan { kPlan128x512 = 0, kPlan128x256Paired = 1, kPlan64x512 = 2, kPlan64x256 = 3, kPlan256x256 = 4 };
 int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus);
+// Estimated time of launch_gemm on a problem of few tiles: rounds of
+// workgroups over the CUs x the measured time of one tile's k loop alone.
+double gemm_alone_us(int64_t rows, int K, int64_t N, int cus);
 // Rows per launch of the MFMA kernel for K in-features and N out-features,
 // or 0 when the shape is beyond its 32-bit buffer offsets: the packed weights
 // must stay below 2^31 bytes, N at most 2^24, and a launch covers a slice of
@@ -120,6 +135,18 @@ inline int64_t gemm_row_slice(int64_t K, int64_t N) {
   const int64_t slice = ((by_q < by_y ? by_q : by_y) / 256) * 256;
   return slice < 256 ? 0 : slice;
 }
+
+// Few token rows (skinny.hip): int8 MFMA with K split over the waves of a
+// workgroup.  `tiled`: q is in the TiledQ layout instead of rows.
+struct SkinnyPlan {
+  int fm = 0, fn = 0;  // 16-row and 16-column blocks of a workgroup's tile
+  double cost = 0.0;
+};
+SkinnyPlan skinny_plan(int64_t M, int K, int64_t N, Epilogue ep, int cus);
+// Whether the automatic path runs the contraction of M rows on it rather than
+// on launch_gemm's tiles.
+bool skinny_takes(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus);
+hipError_t launch_skinny(const ContractArgs& a, bool tiled, hipStream_t stream);
 
 // Interleave the packed gate and up projections of a GLU, [K/16][L] each,
 // into [K/16][2L] blocks of 16 columns (gate, up, gate, ...); L % 16 == 0.

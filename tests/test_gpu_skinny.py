@@ -1,0 +1,153 @@
+"""K-split contraction of few token rows (skinny.hip) on the GPU.
+
+Its int32 sums are exact and its epilogues evaluate the same expressions as the
+tiled MFMA kernel's, so every output must equal the forced GEMM path's bit for
+bit (that path is held to the oracle in test_gpu_parity.py, test_gpu_glu.py and
+test_gpu_mlgru.py); the integer form is also checked against a plain int64
+product here.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mmf():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a HIP device")
+    import paper_2406_02528_amd as m
+    return m
+
+
+def both_paths(mmf, run):
+    """run() on the automatic and on the forced GEMM path; outputs start as NaN."""
+    out = []
+    for path in (mmf.MMF_PATH_AUTO, mmf.MMF_PATH_GEMM):
+        prev = mmf.mmf_set_path(path)
+        try:
+            out.append(run().cpu())
+        finally:
+            mmf.mmf_set_path(prev)
+    return out
+
+
+def nan(*shape):
+    return torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+
+
+def same(a, b):
+    return a.shape == b.shape and not torch.isnan(a).any() and torch.equal(a, b)
+
+
+def weights(mmf, N, K, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return mmf.ternarize(torch.randn(N, K, generator=g, device="cuda") * 0.02)
+
+
+# Row blocks of one to four 16-row fragments and several row blocks, their last
+# one partly filled; column strips of 1, 2, 4 and 8 blocks with ragged ends, N
+# odd and N % 4 == 2; K with a last step of 16, 32 and 48 features, fewer steps
+# than waves, and more than two steps per wave.
+SHAPES = [(17, 16, 100), (17, 1040, 1000), (31, 2064, 6000), (33, 2096, 2044), (45, 5632, 2048), (47, 2080, 11266),
+          (64, 528, 301), (65, 1024, 4096), (70, 4112, 260), (100, 2048, 11264), (129, 1072, 3001), (257, 2048, 1000),
+          (400, 112, 48), (1, 16400, 96), (5, 13824, 324), (16, 13824, 5120), (33, 1024, 5)]
+
+
+@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("f32", [False, True])
+def test_forward_equals_the_gemm_path(mmf, M, K, N, f32):
+    print(f"forward M={M} K={K} N={N} f32={f32}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn(M, K, generator=g, device="cuda")
+    x = x if f32 else x.bfloat16()
+    gamma = torch.rand(K, generator=g, device="cuda") + 0.5
+    Wp, ws = weights(mmf, N, K, 8)
+    w = torch.empty(mmf.mmf_bitlinear_workspace_bytes(M, K), dtype=torch.uint8, device="cuda")
+
+    def run():
+        y = nan(M, N)
+        w.fill_(0x55)  # nothing may be read from the scratch before it is written
+        mmf.mmf_bitlinear_fwd_ws(x, gamma, Wp, ws, y, w)
+        return y
+    a, b = both_paths(mmf, run)
+    assert same(a, b)
+    # the allocating form takes the same route
+    assert torch.equal(mmf.bitlinear(x, gamma, Wp, ws).cpu(), b)
+
+
+@pytest.mark.parametrize("M,K,N", [(17, 16, 100), (45, 2096, 2044), (100, 1040, 6001), (130, 512, 8192)])
+def test_integer_sums_from_rows_of_q(mmf, M, K, N):
+    print(f"raw M={M} K={K} N={N}", flush=True)
+    rs = np.random.default_rng(3)
+    q = torch.from_numpy(rs.integers(-128, 128, (M, K), dtype=np.int8))
+    W = torch.from_numpy(rs.standard_normal((N, K), dtype=np.float32) * np.float32(0.02))
+    Wp, ws = mmf.ternarize(W.cuda())
+    s = ws.cpu()
+    t = torch.clamp(torch.round(W * (1.0 / s)), -1, 1).to(torch.int64)
+    acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+    mmf.mmf_ternary_gemm_i32(q.cuda(), Wp, acc)
+    assert torch.equal(acc.cpu().to(torch.int64), q.to(torch.int64) @ t.t())
+
+
+@pytest.mark.parametrize("M,K,L", [(17, 16, 16), (33, 1040, 2832), (45, 2048, 5632), (200, 2064, 528), (128, 5120, 1744)])
+def test_glu_equals_the_gemm_path(mmf, M, K, L):
+    print(f"glu M={M} K={K} L={L}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    (Wg, sg), (Wu, su) = weights(mmf, L, K, 1), weights(mmf, L, K, 2)
+    Wgu, s2 = mmf.glu_pack(Wg, Wu), torch.cat([sg, su])
+    w = torch.empty(mmf.mmf_bitlinear_workspace_bytes(M, K), dtype=torch.uint8, device="cuda")
+
+    def run():
+        p = nan(M, L)
+        mmf.mmf_glu_fwd_ws(x, None, Wgu, s2, p, w)
+        return p
+    a, b = both_paths(mmf, run)
+    assert same(a, b)
+
+
+@pytest.mark.parametrize("M,K,d", [(17, 64, 16), (33, 1040, 1040), (45, 2048, 2048), (300, 528, 272)])
+@pytest.mark.parametrize("full", [False, True])
+def test_gates_equal_the_gemm_path(mmf, M, K, d, full):
+    print(f"gates M={M} K={K} d={d} full={full}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    Wp, ws = weights(mmf, 3 * d, K, 4)
+    s3 = torch.cat([ws, ws * 1.5, ws * 0.5])
+    bias = torch.rand(3 * d, generator=g, device="cuda") - 0.5 if full else None
+    lb = torch.rand(d, generator=g, device="cuda") if full else None
+    w = torch.empty(mmf.mmf_mlgru_proj_workspace_bytes(M, K, d), dtype=torch.uint8, device="cuda")
+
+    def run():
+        o = nan(M, 3 * d)
+        mmf.mmf_mlgru_proj(x, None, Wp, s3, bias, lb, o, w)
+        return o
+    a, b = both_paths(mmf, run)
+    assert same(a, b)
+
+
+@pytest.mark.parametrize("M", [20, 45])
+def test_capture_and_replay(mmf, M):
+    """Captured calls replay to the eager result, with caller scratch (K-split
+    kernel) and without (the fused decode launches, which allocate nothing)."""
+    K, N = 2048, 1000
+    g = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    Wp, ws = weights(mmf, N, K, 8)
+    w = torch.empty(mmf.mmf_bitlinear_workspace_bytes(M, K), dtype=torch.uint8, device="cuda")
+    y, z = nan(M, N), nan(20, N)
+    mmf.mmf_bitlinear_fwd_ws(x, None, Wp, ws, y, w)
+    want = y.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mmf.mmf_bitlinear_fwd_ws(x, None, Wp, ws, y, w)
+        mmf.mmf_bitlinear_fwd(x[:20], None, Wp, ws, z)
+    for _ in range(3):
+        y.fill_(float("nan"))
+        z.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(z, want[:20])
