@@ -809,8 +809,9 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
     // array: the recurrence and output gate run in the output projection's
     // prologue (no launch, no o' round trip).  Identical arithmetic to the
     // separate kernels, so identical results.
-    if (T == 1 && (h_last == nullptr || h_last != h0) && fused_decode(M, d, d, true) &&
-        !prefers_skinny(M, d, d, true, mmf::Epilogue::kAffineF32)) {
+    const bool fused_decode_out =
+        fused_decode(M, d, d, true) && !prefers_skinny(M, d, d, true, mmf::Epilogue::kAffineF32);
+    if (T == 1 && (h_last == nullptr || h_last != h0) && fused_decode_out) {
       for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
         const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
         mmf::DecodeArgs a{fcg + m0 * 3 * d, true, gamma_o, nullptr, nullptr, nullptr, Wo, w_scale_o,
@@ -821,6 +822,23 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
         if (mmf::launch_decode(a, stream) != hipSuccess) return MMF_ERR_HIP;
       }
       return MMF_OK;
+    }
+    // More sequences, or the state updated in place: the step and the output
+    // gate in the activation quantisation, whose rows each belong to one
+    // workgroup (no o' round trip, one launch less; the same bits).
+    if (T == 1 && !fused_decode_out && mmf::act_quant_mlgru_fits(static_cast<int>(d))) {
+      const FwdScratch f = fwd_scratch(M, d);
+      char* const qs = scratch + s.q_off;
+      int8_t* q = reinterpret_cast<int8_t*>(qs + f.q_off);
+      float* a_scale = reinterpret_cast<float*>(qs + f.a_off);
+      int32_t* rowsum = reinterpret_cast<int32_t*>(qs + f.r_off);
+      const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
+      const bool tiled = use_skinny(M, d, d, ep, true);
+      if (mmf::launch_act_quant_mlgru(fcg, h0, h_last, gamma_o, q, a_scale, rowsum, M, static_cast<int>(d), stream,
+                                      tiled) != hipSuccess)
+        return MMF_ERR_HIP;
+      const mmf::ContractArgs a{q, a_scale, rowsum, Wo, w_scale_o, o, M, static_cast<int>(d), d, ep, out};
+      return hip_status(tiled ? mmf::launch_skinny(a, true, stream) : contract_mfma(a, stream));
     }
     if (mmf::launch_mlgru_scan(fcg, h0, op, h_last, B, T, d, reinterpret_cast<float*>(scratch + s.scan_off),
                                stream) != hipSuccess)

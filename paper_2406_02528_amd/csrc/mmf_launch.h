@@ -24,6 +24,15 @@ hipError_t launch_act_quant(const void* x, bool x_is_f32, const float* gamma, in
                             float* a_scale, int32_t* q_rowsum, int64_t M, int K,
                             hipStream_t stream, float* rstd = nullptr, bool tiled = false);
 
+// The same on the activations of one MLGRU decode step: x is the output gate
+// o' = g sigmoid(h'), h' = f h_in + (1 - f) c, from the gates fcg [M][3K] (f, c,
+// g); h' goes to h_out (nullptr: not stored; may be h_in).  h_in nullptr: 0.
+// Rows that fit registers only.
+bool act_quant_mlgru_fits(int K);
+hipError_t launch_act_quant_mlgru(const float* fcg, const float* h_in, float* h_out, const float* gamma, int8_t* q,
+                                  float* a_scale, int32_t* q_rowsum, int64_t M, int K, hipStream_t stream,
+                                  bool tiled);
+
 // q_rowsum[m] = sum_k q[m][k].
 hipError_t launch_row_sum(const int8_t* q, int32_t* q_rowsum, int64_t M, int K,
                           hipStream_t stream);
