@@ -12,7 +12,7 @@ bool decode_fits(int64_t mt, int K, int64_t N, bool from_x, bool x_is_f32) {
   // 32-bit offsets: the packed array below 2^31 bytes
   if (static_cast<int64_t>(K / 16) * N * 4 >= (int64_t(1) << 31)) return false;
   if (!from_x) return true;
-  return dec::needed_vp(static_cast<int>(mt), K, x_is_f32) <= 4;
+  return dec::needed_vp(dec::row_waves(static_cast<int>(mt), K, x_is_f32), K, x_is_f32) <= 4;
 }
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {

@@ -32,7 +32,6 @@ namespace dec {
 constexpr int kWaves = 16;
 constexpr int kThreads = kWaves * kWave;  // 1024
 constexpr int kMaxTokens = kDecodeMaxTokens;
-constexpr int kMaxRowWaves = 4;            // waves that normalise one token row
 // column sums of token m at red[m * kRedStride + column]: the odd stride puts
 // the same column of different tokens on different LDS banks
 constexpr int kRedStride = kWave + 1;
@@ -58,6 +57,10 @@ constexpr int vec_elems() { return (S == Src::kF32 || S == Src::kMlgru) ? 4 : 8;
 // compile-time parameter of the kernel (index arithmetic with a run-time
 // group size measured 0.4-0.5 us slower per one-token launch).
 constexpr int row_waves_for(int mt) { return mt <= 4 ? 4 : mt <= 8 ? 2 : 1; }
+// The one exception: a single token whose row is too long for four waves' 4
+// vectors per lane takes all 16 (up to 16384 fp32 elements; the serial steps
+// on each SIMD cost less than the second launch that act-quant would be).
+constexpr int kAllRowWaves = 16;
 
 struct Shared {
   int8_t* q;        // [mt][q_stride]
@@ -591,10 +594,15 @@ hipError_t launch_one(const DecodeArgs& a, hipStream_t stream) {
 }
 
 // vectors of 16 bytes per row thread: ceil(K / E / (G * 64))
-inline int needed_vp(int mt, int K, bool f32) {
-  const int lanes = row_waves_for(mt) * kWave;
+inline int needed_vp(int row_waves, int K, bool f32) {
+  const int lanes = row_waves * kWave;
   const int nvec = K / (f32 ? 4 : 8);
   return (nvec + lanes - 1) / lanes;
+}
+// waves per token row for mt rows of K elements
+inline int row_waves(int mt, int K, bool f32) {
+  const int g = row_waves_for(mt);
+  return mt == 1 && f32 && needed_vp(g, K, f32) > 4 ? kAllRowWaves : g;
 }
 
 // Column blocks per workgroup: as few as keep the grid within one round of
@@ -649,7 +657,12 @@ hipError_t dispatch_vp(const DecodeArgs& a, hipStream_t stream) {
   if constexpr (S == Src::kQuantised) {
     return dispatch_f<G, S, 1, EP>(a, stream);
   } else {
-    const int vp = needed_vp(static_cast<int>(a.M), a.K, S == Src::kF32 || S == Src::kMlgru);
+    const int vp = needed_vp(G, a.K, S == Src::kF32 || S == Src::kMlgru);
+    if constexpr (G == kAllRowWaves) {  // rows past 4 vectors of four waves
+      if (vp <= 2) return dispatch_f<G, S, 2, EP>(a, stream);
+      if (vp <= 4) return dispatch_f<G, S, 4, EP>(a, stream);
+      return hipErrorInvalidValue;
+    }
     if (vp <= 1) return dispatch_f<G, S, 1, EP>(a, stream);
     if (vp <= 2) return dispatch_f<G, S, 2, EP>(a, stream);
     if (vp <= 4) return dispatch_f<G, S, 4, EP>(a, stream);
@@ -659,6 +672,9 @@ hipError_t dispatch_vp(const DecodeArgs& a, hipStream_t stream) {
 
 template <Src S, Epilogue EP>
 hipError_t dispatch(const DecodeArgs& a, hipStream_t stream) {
+  if constexpr (S == Src::kF32 || S == Src::kMlgru) {
+    if (row_waves(static_cast<int>(a.M), a.K, true) == kAllRowWaves) return dispatch_vp<kAllRowWaves, S, EP>(a, stream);
+  }
   switch (row_waves_for(static_cast<int>(a.M))) {
     case 4: return dispatch_vp<4, S, EP>(a, stream);
     case 2: return dispatch_vp<2, S, EP>(a, stream);

@@ -66,3 +66,25 @@ def test_decode_step_equals_its_stages(mmf, B, d, state):
     ws = torch.empty(mmf.mmf_mlgru_workspace_bytes(B, 1, d), dtype=torch.uint8, device="cuda").fill_(0x55)
     mmf.mmf_mlgru_fwd(x, B, 1, gamma, Wf, s3, bias, lb, h_in, h, gamma_o, Wo, so, b_o, o, ws)
     assert torch.equal(h, h_ref) and torch.equal(o, o_ref)
+
+
+# One token whose fp32 row takes all 16 waves of the fused decode kernel (two
+# and four vectors per lane, partly filled), on either side of its range.
+@pytest.mark.parametrize("K,N", [(4096, 100), (4112, 100), (5632, 2048), (8192, 301), (8208, 64), (13824, 5120),
+                                 (16384, 40), (16400, 40)])
+def test_one_token_with_a_long_row(mmf, K, N):
+    print(f"long row K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K)
+    x = torch.randn(1, K, generator=g, device="cuda")
+    gamma = torch.rand(K, generator=g, device="cuda") + 0.5
+    Wp, ws = mmf.ternarize(torch.randn(N, K, generator=g, device="cuda") * 0.02)
+    q = torch.empty((1, K), dtype=torch.int8, device="cuda")
+    a, s = torch.empty(1, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    mmf.mmf_act_quant(x, gamma, q, a, s)
+    want = torch.full((1, N), float("nan"), device="cuda")
+    mmf.mmf_ternary_gemm_dequant(q, a, s, Wp, ws, want)
+    assert torch.equal(mmf.bitlinear(x, gamma, Wp, ws), want)
+    if N % 32 == 0:
+        glu, ref = mmf.glu(x, gamma, Wp, torch.cat([ws, ws])), torch.full((1, N // 2), float("nan"), device="cuda")
+        mmf.mmf_ternary_gemm_glu(q, a, s, Wp, torch.cat([ws, ws]), ref)
+        assert torch.equal(glu, ref)
