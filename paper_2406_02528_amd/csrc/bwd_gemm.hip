@@ -24,7 +24,8 @@
 // would not.  The sum is doubled (exactly) in the epilogue.
 //
 // The dY tile is 128 tokens x 512 input features; 8 waves each own 128 x 64
-// (8 x 4 MFMA tiles), so each expanded code fragment feeds eight MFMAs.  The
+// (8 x 4 MFMA tiles), so each expanded code fragment feeds eight MFMAs (64 x
+// 256 by 4 waves of 64 x 64 where those finish sooner: bwd_dy_plan).  The
 // stage pipeline (3-slot LDS ring, LDS-DMA copies issued one per fragment
 // group, one k64-byte step ahead) is the one of the prefill contraction: the
 // dO rows are 128-byte slices of 64 bf16 values, exactly as the int8 rows of
@@ -102,41 +103,66 @@ __global__ __launch_bounds__(kBlock) void pack_nmajor_kernel(const uint32_t* __r
   Wn[jn * K + k] = w;
 }
 
-// dO rows padded with zeros to a multiple of 8 columns (16-byte chunks).
-__global__ __launch_bounds__(kBlock) void pad_rows_kernel(const uint16_t* __restrict__ src, int64_t M, int64_t N,
-                                                          int64_t N8, uint16_t* __restrict__ dst) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-  if (idx >= M * N8) return;
-  const int64_t m = idx / N8, n = idx % N8;
-  dst[idx] = n < N ? src[m * N + n] : uint16_t(0);
+// dO rows padded with zeros to a multiple of 8 columns (16-byte chunks): one
+// row per blockIdx.x, one 16-byte chunk per thread.  Rows of odd N start on 2
+// bytes, so a chunk inside the row is read as the five dwords that cover it
+// and shifted; the chunk at the row's end element by element.  (One element
+// per thread with a 64-bit division each took 18 us for 1937 x 3998.)
+__global__ __launch_bounds__(kBlock) void pad_rows_kernel(const uint16_t* __restrict__ src, int64_t M, int N, int N8,
+                                                          uint16_t* __restrict__ dst) {
+  const int64_t m = blockIdx.x;
+  const int c = (blockIdx.y * kBlock + threadIdx.x) * 8;
+  if (c >= N8) return;
+  const uint16_t* s = src + m * N;
+  uint32_t w[5];
+  if (c + 9 < N) {
+    // elements c - 1 .. c + 8 or c .. c + 9: inside the array, since c - 1 of
+    // the first row's first chunk is never read (the array is aligned)
+    const uintptr_t at = reinterpret_cast<uintptr_t>(s + c);
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(at & ~uintptr_t(3));
+    const uint32_t sh = (at & 2) ? 16 : 0;
+#pragma unroll
+    for (int i = 0; i < 5; ++i) w[i] = p[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], sh);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t lo = c + 2 * i < N ? s[c + 2 * i] : 0u;
+      const uint32_t hi = c + 2 * i + 1 < N ? s[c + 2 * i + 1] : 0u;
+      w[i] = lo | (hi << 16);
+    }
+  }
+  *reinterpret_cast<uint4*>(dst + m * N8 + c) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ---------------------------------------------------------------------------
 // dY = dO Wt^T with the RMSNorm-backward epilogue
 // ---------------------------------------------------------------------------
-namespace dyk {
-constexpr int BM = 128, BN = 512, WN = 64, BK = 128, S = 3;
-constexpr int kWaves = BN / WN;                        // 8, each over all BM rows
-constexpr int kThreads = kWaves * kWave;
-constexpr int FM = BM / 16, FN = WN / 16;              // 8 x 4 MFMA tiles per wave
-constexpr int KS = BK / 64;                            // 32-value steps per stage (64 bytes each)
-constexpr int kABytes = BM * BK;
-constexpr int kAInstr = kABytes / 1024;
-constexpr int kRowsPerInstr = 1024 / BK;
-constexpr int kWordRows = BK / 32;                     // 64 n per stage = 4 n-major word rows
-constexpr int kBRow = BN + 16;                         // padded word row
-constexpr int kBBytes = kWordRows * kBRow * 4;
-constexpr int kBInstr = kWordRows * BN / 256;
-constexpr int kAPerWave = kAInstr / kWaves, kBPerWave = kBInstr / kWaves;
-constexpr int kLoadsPerStage = kAPerWave + kBPerWave;
-constexpr int kStageBytes = kABytes + kBBytes;
-static_assert(kAInstr % kWaves == 0 && kBInstr % kWaves == 0, "loads must split evenly");
-static_assert(kLoadsPerStage <= FM, "one stage load per fragment group");
-static_assert(FN == 4 && FM >= 2 * FN, "expansion schedule: four words, one per late fragment");
-static_assert(S * kStageBytes >= kWaves * 4 * BM * 8, "row-sum reduction reuses the ring");
-constexpr int kDbRedBytes = kWaves * kWave * 8;        // per-wave fp64 scratch of the db column sums
-static_assert(BK == 128 && kWaves == 8 && BM == 128, "db duty: wave w sums chunk w of every row");
-}  // namespace dyk
+template <int BM_, int BN_>
+struct DyTile {
+  static constexpr int BM = BM_, BN = BN_, WN = 64, BK = 128, S = 3;
+  static constexpr int kWaves = BN / WN;                 // each over all BM rows
+  static constexpr int kThreads = kWaves * kWave;
+  static constexpr int FM = BM / 16, FN = WN / 16;       // MFMA tiles per wave
+  static constexpr int KS = BK / 64;                     // 32-value steps per stage (64 bytes each)
+  static constexpr int kABytes = BM * BK;
+  static constexpr int kAInstr = kABytes / 1024;
+  static constexpr int kRowsPerInstr = 1024 / BK;
+  static constexpr int kWordRows = BK / 32;              // 64 n per stage = 4 n-major word rows
+  static constexpr int kBRow = BN + 16;                  // padded word row
+  static constexpr int kBBytes = kWordRows * kBRow * 4;
+  static constexpr int kBInstr = kWordRows * BN / 256;
+  static constexpr int kAPerWave = kAInstr / kWaves, kBPerWave = kBInstr / kWaves;
+  static constexpr int kLoadsPerStage = kAPerWave + kBPerWave;
+  static constexpr int kStageBytes = kABytes + kBBytes;
+  static constexpr int kDbRedBytes = kWaves * kWave * 8;  // per-wave fp64 scratch of the db column sums
+  static_assert(kAInstr % kWaves == 0 && kBPerWave == 1, "loads must split evenly");
+  static_assert(kLoadsPerStage <= FM, "one stage load per fragment group");
+  static_assert(FN == 4 && FM >= FN, "expansion schedule: four words behind the fragment groups");
+  static_assert(S * kStageBytes >= kWaves * 4 * BM * 8, "row-sum reduction reuses the ring");
+  static_assert(BK == 128 && 8 % kWaves == 0, "db duty: wave w sums chunks w, w + kWaves, ... of every row");
+};
 
 // Expanded code fragment of one lane: 8 bf16 values t / 2 (see the file head).
 __device__ __forceinline__ v4i expand_bf16_half(uint32_t w, uint32_t rot) {
@@ -183,14 +209,17 @@ template <> struct X4<float> {
 // the 16 rows g8 + 8 i in fp64 (bf16 values are exact in fp64), then the 8
 // row groups are added in order through the wave's own LDS scratch and the
 // sum goes to db_part[tm][n].
-template <typename XT>
-__global__ __launch_bounds__(dyk::kThreads) void dy_kernel(
+template <typename XT, typename T>
+__global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(2))) void dy_kernel(
     const uint16_t* __restrict__ dO, const uint32_t* __restrict__ Wn, const float* __restrict__ w_scale,
     const XT* __restrict__ x, const float* __restrict__ gamma, const float* __restrict__ rstd,
     float* __restrict__ rg, double* __restrict__ s_part, int64_t ld_s, double* __restrict__ dg_part,
     double* __restrict__ db_part, int M, int N, int Np, int K) {
-  using namespace dyk;
-  __shared__ __attribute__((aligned(16))) char smem[S * kStageBytes + kDbRedBytes];
+  constexpr int BM = T::BM, BN = T::BN, WN = T::WN, BK = T::BK, S = T::S, FM = T::FM, FN = T::FN, KS = T::KS;
+  constexpr int kWaves = T::kWaves, kABytes = T::kABytes, kRowsPerInstr = T::kRowsPerInstr;
+  constexpr int kWordRows = T::kWordRows, kBRow = T::kBRow, kAPerWave = T::kAPerWave;
+  constexpr int kLoadsPerStage = T::kLoadsPerStage, kStageBytes = T::kStageBytes;
+  __shared__ __attribute__((aligned(16))) char smem[S * kStageBytes + T::kDbRedBytes];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wn = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -260,6 +289,14 @@ __global__ __launch_bounds__(dyk::kThreads) void dy_kernel(
     return Bs[(ks * 2 + (g >> 1)) * kBRow + wn * WN + f * 16 + l16];
   };
 
+  constexpr auto exp_lo = [](int fm) constexpr -> int {
+    if constexpr (FM >= 2 * FN) return fm >= FM - FN ? fm - (FM - FN) : 0;
+    else return fm == 0 ? 0 : ((fm - 1) * FN) / (FM - 1);
+  };
+  constexpr auto exp_hi = [](int fm) constexpr -> int {
+    if constexpr (FM >= 2 * FN) return fm >= FM - FN ? fm - (FM - FN) + 1 : 0;
+    else return fm == 0 ? 0 : (fm * FN) / (FM - 1);
+  };
 #pragma unroll
   for (int p = 0; p < S - 1; ++p)
 #pragma unroll
@@ -280,20 +317,24 @@ __global__ __launch_bounds__(dyk::kThreads) void dy_kernel(
   auto db_stage = [&](int kt) {
     const char* st = smem + (kt % S) * kStageBytes;
     const int dc = lane & 7, g8 = lane >> 3;
-    double sum = 0.0;
 #pragma unroll
-    for (int i = 0; i < BM / 8; ++i) {
-      const int r = g8 + 8 * i;
-      const uint32_t v = *reinterpret_cast<const uint16_t*>(st + r * BK + ((wn ^ a_swz(r)) << 4) + 2 * dc);
-      sum += static_cast<double>(__uint_as_float(v << 16));
-    }
-    db_red[lane] = sum;
-    if (lane < 8) {
-      double t = 0.0;
+    for (int c = 0; c < 8 / kWaves; ++c) {
+      const int ch = wn + c * kWaves;
+      double sum = 0.0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) t += db_red[8 * j + lane];
-      const int n = kt * (BK / 2) + wn * 8 + lane;
-      if (n < N) db_part[tm * N + n] = t;
+      for (int i = 0; i < BM / 8; ++i) {
+        const int r = g8 + 8 * i;
+        const uint32_t v = *reinterpret_cast<const uint16_t*>(st + r * BK + ((ch ^ a_swz(r)) << 4) + 2 * dc);
+        sum += static_cast<double>(__uint_as_float(v << 16));
+      }
+      db_red[lane] = sum;
+      if (lane < 8) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) t += db_red[8 * j + lane];
+        const int n = kt * (BK / 2) + ch * 8 + lane;
+        if (n < N) db_part[tm * N + n] = t;
+      }
     }
   };
 
@@ -318,7 +359,10 @@ __global__ __launch_bounds__(dyk::kThreads) void dy_kernel(
       for (int f = 0; f < FN; ++f) acc[fm][f] = mfma_bf16(bc[f], af[fm], acc[fm][f]);
       af[fm] = a_read(s + 1, fm);
       if (refill && fm < kLoadsPerStage) issue_one(kt + S - 1, fm);
-      if (fm >= FM - FN) bn[fm - (FM - FN)] = expand_bf16_half(bw[fm - (FM - FN)], rot);
+      // the next step's words: one behind each of the last FN groups, or
+      // spread over groups 1 .. FM - 1 (group 0 leaves their LDS reads time)
+#pragma unroll
+      for (int f = exp_lo(fm); f < exp_hi(fm); ++f) bn[f] = expand_bf16_half(bw[f], rot);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (refill && db_part != nullptr && kt % ntn == tn) db_stage(kt);
@@ -842,15 +886,37 @@ hipError_t launch_pack_nmajor(const uint32_t* Wpacked, int64_t N, int64_t Np, in
 }
 
 hipError_t launch_pad_rows(const uint16_t* src, int64_t M, int64_t N, int64_t N8, uint16_t* dst, hipStream_t stream) {
-  const int64_t total = M * N8;
-  if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(pad_rows_kernel, dim3(static_cast<unsigned>((total + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                     stream, src, M, N, N8, dst);
+  if (M * N8 == 0) return hipSuccess;
+  hipLaunchKernelGGL(pad_rows_kernel, dim3(static_cast<unsigned>(M), static_cast<unsigned>((N8 / 8 + kBlock - 1) / kBlock)),
+                     dim3(kBlock), 0, stream, src, M, static_cast<int>(N), static_cast<int>(N8), dst);
   return hipGetLastError();
 }
 
-int64_t bwd_dy_col_tiles(int64_t K) { return (K + dyk::BN - 1) / dyk::BN; }
-int64_t bwd_dy_row_tiles(int64_t M) { return (M + dyk::BM - 1) / dyk::BM; }
+DyPlan bwd_dy_plan(int64_t M, int64_t K, int cus) {
+  // 128 x 512 tiles, one workgroup per CU, take one k loop per round of tiles
+  // over the CUs.  64 x 256 tiles, a quarter of the area each and up to three
+  // per CU, move twice the operand bytes per MAC but fill the chip where
+  // there are few tiles, and leave less of it idle in a partial last round.
+  // Their time for n of them per CU, in units of the wide tile's round
+  // (measured, M x K x N: wide / small, us of the whole backward):
+  //   n = 1  1000 x 1024 x 4096  163 / 111     n = 2  4096 x 2048 x 11264 512 / 451
+  //   n = 2  1937 x 2288 x 4000  200 / 173     n = 4  5000 x 2560 x 2560  204 / 229
+  //   n = 3  16384 x 768 x 768   140 / 135     n = 4  8192 x 2048 x 11264 737 / 826
+  //   n = 5  6000 x 3072 x 1024  192 / 179     n = 6  12000 x 2048 x 1024 217 / 208
+  constexpr double kSmall[] = {0.0, 0.55, 0.78, 1.0, 1.31, 1.65, 1.9};
+  const int64_t c = cus > 0 ? cus : 256;
+  const int64_t wide = ((M + 127) / 128) * ((K + 511) / 512), small = ((M + 63) / 64) * ((K + 255) / 256);
+  const int64_t n = (small + c - 1) / c;
+  const double t_small = n <= 6 ? kSmall[n] : 0.32 * static_cast<double>(n);
+  DyPlan p;
+  if (t_small <= static_cast<double>((wide + c - 1) / c)) {
+    p.bm = 64;
+    p.bn = 256;
+  }
+  p.row_tiles = (M + p.bm - 1) / p.bm;
+  p.col_tiles = (K + p.bn - 1) / p.bn;
+  return p;
+}
 
 int64_t bwd_dy_row_slice(int64_t Np, int64_t K) {
   // 32-bit buffer offsets: dO rows (2 Np bytes each) and n-major words of
@@ -858,37 +924,45 @@ int64_t bwd_dy_row_slice(int64_t Np, int64_t K) {
   const int64_t lim = (int64_t(1) << 31) - 1;
   if (((Np + 15) / 16) * K * 4 > lim) return 0;
   int64_t rows = lim / (2 * Np);
-  rows = rows / dyk::BM * dyk::BM;
+  rows = rows / 128 * 128;
   return rows;
 }
 
-hipError_t launch_dy(const uint16_t* dO, int64_t M, int64_t N, int64_t Np, const uint32_t* Wn,
-                     const float* w_scale, const void* x, bool x_is_f32, const float* gamma, const float* rstd,
-                     int K, float* rg, double* s_part, double* dg_part, double* db_part, hipStream_t stream) {
-  const int64_t slice = bwd_dy_row_slice(Np, K);
-  if (slice == 0) return hipErrorInvalidValue;
-  for (int64_t mb = 0; mb < M; mb += slice) {
-    const int64_t rows = M - mb < slice ? M - mb : slice;
-    const dim3 grid(static_cast<unsigned>(bwd_dy_row_tiles(rows) * bwd_dy_col_tiles(K)));
-    double* dgp = dg_part ? dg_part + (mb / dyk::BM) * K : nullptr;
-    double* dbp = db_part ? db_part + (mb / dyk::BM) * N : nullptr;
-    if (x_is_f32)
-      hipLaunchKernelGGL(dy_kernel<float>, grid, dim3(dyk::kThreads), 0, stream, dO + mb * Np, Wn, w_scale,
-                         static_cast<const float*>(x) + mb * K, gamma, rstd + mb, rg + mb * K, s_part + mb, M,
-                         dgp, dbp, static_cast<int>(rows), static_cast<int>(N), static_cast<int>(Np), K);
-    else
-      hipLaunchKernelGGL(dy_kernel<uint16_t>, grid, dim3(dyk::kThreads), 0, stream, dO + mb * Np, Wn, w_scale,
-                         static_cast<const uint16_t*>(x) + mb * K, gamma, rstd + mb, rg + mb * K, s_part + mb, M,
-                         dgp, dbp, static_cast<int>(rows), static_cast<int>(N), static_cast<int>(Np), K);
-  }
+template <typename XT, typename T>
+static hipError_t launch_dy_tile(const DyArgs& a, int64_t mb, int64_t rows, hipStream_t stream) {
+  const int64_t rt = mb / T::BM;  // row tiles before this slice
+  const int64_t tiles = ((rows + T::BM - 1) / T::BM) * ((a.K + T::BN - 1) / T::BN);
+  hipLaunchKernelGGL((dy_kernel<XT, T>), dim3(static_cast<unsigned>(tiles)), dim3(T::kThreads), 0, stream,
+                     a.dO + mb * a.Np, a.Wn, a.w_scale, static_cast<const XT*>(a.x) + mb * a.K, a.gamma, a.rstd + mb,
+                     a.rg + mb * a.K, a.s_part + mb, a.M, a.dg_part ? a.dg_part + rt * a.K : nullptr,
+                     a.db_part ? a.db_part + rt * a.N : nullptr, static_cast<int>(rows), static_cast<int>(a.N),
+                     static_cast<int>(a.Np), a.K);
   return hipGetLastError();
 }
 
+template <typename XT>
+static hipError_t launch_dy_x(const DyArgs& a, const DyPlan& p, int64_t mb, int64_t rows, hipStream_t stream) {
+  if (p.bm == 64) return launch_dy_tile<XT, DyTile<64, 256>>(a, mb, rows, stream);
+  return launch_dy_tile<XT, DyTile<128, 512>>(a, mb, rows, stream);
+}
+
+hipError_t launch_dy(const DyArgs& a, const DyPlan& p, hipStream_t stream) {
+  const int64_t slice = bwd_dy_row_slice(a.Np, a.K);
+  if (slice == 0) return hipErrorInvalidValue;
+  for (int64_t mb = 0; mb < a.M; mb += slice) {
+    const int64_t rows = a.M - mb < slice ? a.M - mb : slice;
+    const hipError_t e = a.x_is_f32 ? launch_dy_x<float>(a, p, mb, rows, stream)
+                                    : launch_dy_x<uint16_t>(a, p, mb, rows, stream);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_dx_finish(float* dx, const void* x, bool x_is_f32, const float* rstd, const double* s_part,
-                            int64_t M, int K, hipStream_t stream) {
+                            int64_t col_tiles, int64_t M, int K, hipStream_t stream) {
   const int64_t total = M * K / 4;
   if (total == 0) return hipSuccess;
-  const int nkt = static_cast<int>(bwd_dy_col_tiles(K));
+  const int nkt = static_cast<int>(col_tiles);
   const dim3 grid(static_cast<unsigned>((total + kBlock - 1) / kBlock));
   if (x_is_f32)
     hipLaunchKernelGGL(dx_finish_kernel<float>, grid, dim3(kBlock), 0, stream, dx, static_cast<const float*>(x), rstd,
@@ -897,14 +971,6 @@ hipError_t launch_dx_finish(float* dx, const void* x, bool x_is_f32, const float
     hipLaunchKernelGGL(dx_finish_kernel<uint16_t>, grid, dim3(kBlock), 0, stream, dx,
                        static_cast<const uint16_t*>(x), rstd, s_part, nkt, M, K);
   return hipGetLastError();
-}
-
-hipError_t launch_dgamma_finish(const double* dg_part, int64_t M, int K, float* dgamma, hipStream_t stream) {
-  return launch_col_final(dg_part, bwd_dy_row_tiles(M), K, dgamma, stream);
-}
-
-hipError_t launch_db_finish(const double* db_part, int64_t M, int64_t N, float* db, hipStream_t stream) {
-  return launch_col_final(db_part, bwd_dy_row_tiles(M), N, db, stream);
 }
 
 DwPlan bwd_dw_plan(int64_t M, int64_t N, int64_t K, int64_t Np, int cus) {

@@ -407,21 +407,23 @@ TrainScratch train_scratch(int64_t M, int64_t K, int64_t N) {
 struct BwdScratch {
   int64_t Np;
   mmf::DwPlan plan;
+  mmf::DyPlan dy;
   size_t wn_off, dop_off, spart_off, dgpart_off, dbpart_off, dw_off, parts_off, total;
 };
 BwdScratch bwd_scratch(int64_t M, int64_t K, int64_t N) {
   BwdScratch s;
   s.Np = (N + 7) / 8 * 8;
   s.plan = mmf::bwd_dw_plan(M, N, K, s.Np, mmf::device_cus());
+  s.dy = mmf::bwd_dy_plan(M, K, mmf::device_cus());
   s.wn_off = 0;
   s.dop_off = round_up(static_cast<size_t>(mmf::bwd_nmajor_words(N, K)) * 4, kScratchAlign);
   const size_t dop = s.Np != N ? static_cast<size_t>(M) * static_cast<size_t>(s.Np) * 2 : 0;
   s.spart_off = s.dop_off + round_up(dop, kScratchAlign);
-  s.dgpart_off = s.spart_off + round_up(sizeof(double) * static_cast<size_t>(mmf::bwd_dy_col_tiles(K) * M),
+  s.dgpart_off = s.spart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.col_tiles * M),
                                         kScratchAlign);
-  s.dbpart_off = s.dgpart_off + round_up(sizeof(double) * static_cast<size_t>(mmf::bwd_dy_row_tiles(M) * K),
+  s.dbpart_off = s.dgpart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.row_tiles * K),
                                           kScratchAlign);
-  s.dw_off = s.dbpart_off + round_up(sizeof(double) * static_cast<size_t>(mmf::bwd_dy_row_tiles(M) * N),
+  s.dw_off = s.dbpart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.row_tiles * N),
                                       kScratchAlign);
   const int64_t S = s.plan.split_all;
   s.parts_off = s.dw_off + (S > 1 ? round_up(sizeof(float) * static_cast<size_t>(S * N * K), kScratchAlign) : 0);
@@ -919,11 +921,12 @@ int mmf_bitlinear_bwd(const uint16_t* dO, const void* x, int x_is_f32, const flo
     // then dx and dgamma finished
     if (mmf::launch_pack_nmajor(Wpacked, N, s.Np, Ki, Wn, stream) != hipSuccess) return MMF_ERR_HIP;
     double* db_part = db ? reinterpret_cast<double*>(scratch + s.dbpart_off) : nullptr;
-    if (mmf::launch_dy(dOp, M, N, s.Np, Wn, w_scale, x, f32, gamma, rstd, Ki, dx, s_part, dg_part, db_part,
-                       stream) != hipSuccess)
+    const mmf::DyArgs dy{dOp, M, N, s.Np, Wn, w_scale, x, f32, gamma, rstd, Ki, dx, s_part, dg_part, db_part};
+    if (mmf::launch_dy(dy, s.dy, stream) != hipSuccess) return MMF_ERR_HIP;
+    if (mmf::launch_dx_finish(dx, x, f32, rstd, s_part, s.dy.col_tiles, M, Ki, stream) != hipSuccess)
       return MMF_ERR_HIP;
-    if (mmf::launch_dx_finish(dx, x, f32, rstd, s_part, M, Ki, stream) != hipSuccess) return MMF_ERR_HIP;
-    if (dgamma && mmf::launch_dgamma_finish(dg_part, M, Ki, dgamma, stream) != hipSuccess) return MMF_ERR_HIP;
+    if (dgamma && mmf::launch_col_final(dg_part, s.dy.row_tiles, K, dgamma, stream) != hipSuccess)
+      return MMF_ERR_HIP;
     // dW = dO^T Yq (token range split into parts when the output has few
     // tiles; the last partial round of tiles spread over all CUs otherwise)
     const int64_t S = s.plan.split_all;
@@ -932,7 +935,7 @@ int mmf_bitlinear_bwd(const uint16_t* dO, const void* x, int x_is_f32, const flo
     if (mmf::launch_dw(dOp, q, a_scale, M, s.Np, N, Ki, dw_out, parts, s.plan, stream) != hipSuccess)
       return MMF_ERR_HIP;
     if (S > 1 && mmf::launch_sum_parts(dw_out, S, N * K, dW, stream) != hipSuccess) return MMF_ERR_HIP;
-    if (db && mmf::launch_db_finish(db_part, M, N, db, stream) != hipSuccess) return MMF_ERR_HIP;
+    if (db && mmf::launch_col_final(db_part, s.dy.row_tiles, N, db, stream) != hipSuccess) return MMF_ERR_HIP;
     return MMF_OK;
   });
 }

@@ -185,22 +185,33 @@ hipError_t launch_pack_nmajor(const uint32_t* Wpacked, int64_t N, int64_t Np, in
 hipError_t launch_pad_rows(const uint16_t* src, int64_t M, int64_t N, int64_t N8, uint16_t* dst,
                            hipStream_t stream);
 // dY kernel: dO [M][Np] bf16 (Np % 8 == 0) against Wn; writes rg = r gamma dY
-// into rg [M][K], s_part [bwd_dy_col_tiles(K)][M] and (if not null) dg_part
-// [bwd_dy_row_tiles(M)][K] and db_part [bwd_dy_row_tiles(M)][N] (the column
-// sums of dO per row tile, for db).  bwd_dy_row_slice(Np, K) == 0: shape not
+// into rg [M][K], s_part [col_tiles][M] and (if not null) dg_part
+// [row_tiles][K] and db_part [row_tiles][N] (the column sums of dO per row
+// tile, for db), on bm x bn tiles.  bwd_dy_row_slice(Np, K) == 0: shape not
 // supported (32-bit offsets).
-int64_t bwd_dy_col_tiles(int64_t K);
-int64_t bwd_dy_row_tiles(int64_t M);
+struct DyPlan {
+  int bm = 128, bn = 512;
+  int64_t row_tiles = 0, col_tiles = 0;
+};
+DyPlan bwd_dy_plan(int64_t M, int64_t K, int cus);
 int64_t bwd_dy_row_slice(int64_t Np, int64_t K);
-hipError_t launch_dy(const uint16_t* dO, int64_t M, int64_t N, int64_t Np, const uint32_t* Wn,
-                     const float* w_scale, const void* x, bool x_is_f32, const float* gamma, const float* rstd,
-                     int K, float* rg, double* s_part, double* dg_part, double* db_part, hipStream_t stream);
-// dx = rg - (r^3 s / K) x in place; dgamma from the row-tile partials.
+struct DyArgs {
+  const uint16_t* dO;
+  int64_t M, N, Np;
+  const uint32_t* Wn;
+  const float* w_scale;
+  const void* x;
+  bool x_is_f32;
+  const float* gamma;
+  const float* rstd;
+  int K;
+  float* rg;
+  double *s_part, *dg_part, *db_part;
+};
+hipError_t launch_dy(const DyArgs& a, const DyPlan& p, hipStream_t stream);
+// dx = rg - (r^3 s / K) x in place, s the sum of the row's col_tiles partials.
 hipError_t launch_dx_finish(float* dx, const void* x, bool x_is_f32, const float* rstd, const double* s_part,
-                            int64_t M, int K, hipStream_t stream);
-hipError_t launch_dgamma_finish(const double* dg_part, int64_t M, int K, float* dgamma, hipStream_t stream);
-// db[n] = sum over the row tiles of db_part (fp64, tile order).
-hipError_t launch_db_finish(const double* db_part, int64_t M, int64_t N, float* db, hipStream_t stream);
+                            int64_t col_tiles, int64_t M, int K, hipStream_t stream);
 // Work units of the dW kernel.  split_all > 1: every tile's token range is
 // split into split_all parts, written to out [split_all][N][K] and added by
 // launch_sum_parts.  Otherwise tiles [0, full) are whole units and the
