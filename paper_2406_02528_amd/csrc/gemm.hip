@@ -7,8 +7,7 @@
 // the code c = t + 1 in {0,1,2}; the epilogue subtracts sum_k q (sum q*t =
 // sum q*c - sum q) and dequantises.
 //
-// Tiling: a workgroup of 8 waves computes a 128 x 512 output tile (256 x 256
-// when N % 4 != 0); wave (wm, wn) owns a 128 x 64 block as 8 x 4 MFMA tiles
+// Tiling: a workgroup of 8 waves computes a 128 x 512 output tile; wave (wm, wn) owns a 128 x 64 block as 8 x 4 MFMA tiles
 // of 16 x 16.  Each expanded weight fragment therefore feeds eight MFMAs,
 // which keeps the VALU work of the 2-bit expansion small against the matrix
 // work.  The wide tile moves fewer operand bytes per MAC into LDS than a
@@ -103,7 +102,11 @@ struct Tiling {
 // Two waves per SIMD whatever the workgroup size: a 4-wave workgroup left to
 // itself would take up to 512 registers per lane and keep a second workgroup
 // off its CU.
-template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4, Epilogue EP>
+// RAG: N % 4 != 0 on the 16-byte B copies.  Buffer loads (into LDS too) need
+// dword alignment only and are range-checked dword by dword, so the word rows
+// may start anywhere; a lane's four outputs are stored one by one where they
+// cross the row's end.
+template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4, Epilogue EP, bool RAG = false>
 __global__ __launch_bounds__((Tiling<BM, BN, WM, WN, BK, S, BX4>::kThreads))
 __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
     const int8_t* __restrict__ q, const float* __restrict__ a_scale,
@@ -440,6 +443,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
   // that way and keep direct 16-byte stores, and N % 4 != 0 takes
   // per-element stores.
   constexpr bool kStaged = BX4 && (EP == Epilogue::kDequantF32 || EP == Epilogue::kRawI32);
+  static_assert(!RAG || kStaged, "ragged rows leave through the staged stores");
   if constexpr (!kStaged) {
     const int ow = kGlu ? N / 2 : N;  // output row length
     const uint32_t out_bytes = static_cast<uint32_t>(M) * static_cast<uint32_t>(ow) * 4u;
@@ -503,12 +507,43 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
         const v4i v = *reinterpret_cast<const v4i*>(buf + (4 * i + rr) * kRowB + qq * 16);
         const int m = m0 + wm * WM + fm * 16 + 4 * i + rr;
         const uint32_t off =
-            (m < M && n < ow) ? (static_cast<uint32_t>(m) * static_cast<uint32_t>(ow) + static_cast<uint32_t>(n)) * 4u
-                              : kOut;
+            (m < M && n + (RAG ? 3 : 0) < ow)
+                ? (static_cast<uint32_t>(m) * static_cast<uint32_t>(ow) + static_cast<uint32_t>(n)) * 4u
+                : kOut;
         __builtin_amdgcn_raw_buffer_store_b128(v, orsrc, off, 0, 0);
+        if constexpr (RAG) {
+          if (m < M && n < ow && n + 3 >= ow) {
+            const uint32_t at = (static_cast<uint32_t>(m) * static_cast<uint32_t>(ow) + static_cast<uint32_t>(n)) * 4u;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+              if (n + r < ow)
+                __builtin_amdgcn_raw_buffer_store_b32(static_cast<uint32_t>(v[r]), orsrc, at + 4u * r, 0, 0);
+          }
+        }
       }
     }
   }
+}
+
+template <int BM, int BN, int WM, int WN, int BK, int S>
+hipError_t launch_ragged(const ContractArgs& a, int64_t m_begin, int64_t m_rows, hipStream_t stream) {
+  using T = Tiling<BM, BN, WM, WN, BK, S, true>;
+  const dim3 grid(static_cast<unsigned>(((m_rows + BM - 1) / BM) * ((a.N + BN - 1) / BN)));
+  const int8_t* q = a.q + m_begin * a.K;
+  const float* as = a.a_scale ? a.a_scale + m_begin : nullptr;
+  const int32_t* rs = a.q_rowsum + m_begin;
+  void* out = static_cast<int32_t*>(a.out) + m_begin * a.N;  // four-byte elements in both forms
+  if (a.epilogue == Epilogue::kDequantF32)
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, BK, S, true, Epilogue::kDequantF32, true>), grid,
+                       dim3(T::kThreads), 0, stream, q, as, rs, a.Wpacked, a.w_scale, out, static_cast<int>(m_rows),
+                       a.K, static_cast<int>(a.N), a.affine);
+  else if (a.epilogue == Epilogue::kRawI32)
+    hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, BK, S, true, Epilogue::kRawI32, true>), grid, dim3(T::kThreads),
+                       0, stream, q, as, rs, a.Wpacked, a.w_scale, out, static_cast<int>(m_rows), a.K,
+                       static_cast<int>(a.N), a.affine);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4>
@@ -599,17 +634,22 @@ int gemm_tile_choice(int64_t rows, int64_t N, int cus) {
   return best;
 }
 
+// N % 4 != 0: rows of one 256 x 256 tile keep that tile's 4-byte copies (so few
+// rows come here on the forced path only); more take the plan of any other N
+// (ragged stores), measured at 1937 x 2288 x 3998 45 -> 21 us.
+constexpr int64_t kRaggedMinRows = 257;
+
 double gemm_alone_us(int64_t rows, int K, int64_t N, int cus) {
   struct Shape { int64_t bm, bn; double us, us_per_k; };
   constexpr Shape kShapes[] = {
       {128, 512, 3.2, 0.0099}, {64, 512, 3.2, 0.0066}, {64, 256, 3.2, 0.0038}, {256, 256, 8.0, 0.0125}};
-  const Shape& s = kShapes[N % 4 != 0 ? 3 : gemm_tile_choice(rows, N, cus)];
+  const Shape& s = kShapes[N % 4 != 0 && rows < kRaggedMinRows ? 3 : gemm_tile_choice(rows, N, cus)];
   const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), c = cus > 0 ? cus : 256;
   return static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K);
 }
 
 int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus) {
-  if (N % 4 != 0) return kPlan256x256;
+  if (N % 4 != 0 && rows < kRaggedMinRows) return kPlan256x256;
   const int choice = gemm_tile_choice(rows, N, cus);
   if (choice == 1) return kPlan64x512;
   if (choice == 2) return kPlan64x256;
@@ -626,7 +666,18 @@ hipError_t launch_gemm(const ContractArgs& a, hipStream_t stream) {
   for (int64_t m0 = 0; m0 < a.M; m0 += slice) {
     const int64_t rows = a.M - m0 < slice ? a.M - m0 : slice;
     hipError_t e;
-    switch (gemm_plan(rows, a.K, a.N, a.epilogue, cus)) {
+    const int plan = gemm_plan(rows, a.K, a.N, a.epilogue, cus);
+    if (a.N % 4 != 0 && plan != kPlan256x256) {
+      switch (plan) {
+        case kPlan64x512: e = launch_ragged<64, 512, 64, 64, 128, 3>(a, m0, rows, stream); break;
+        case kPlan64x256: e = launch_ragged<64, 256, 32, 64, 128, 3>(a, m0, rows, stream); break;
+        case kPlan128x256Paired: e = launch_ragged<128, 256, 128, 64, 128, 3>(a, m0, rows, stream); break;
+        default: e = launch_ragged<128, 512, 128, 64, 128, 3>(a, m0, rows, stream); break;
+      }
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    switch (plan) {
       case kPlan256x256: e = launch_cfg<256, 256, 128, 64, 128, 3, false>(a, m0, rows, stream); break;
       case kPlan64x512: e = launch_cfg<64, 512, 64, 64, 128, 3, true>(a, m0, rows, stream); break;
       case kPlan64x256: e = launch_cfg<64, 256, 32, 64, 128, 3, true>(a, m0, rows, stream); break;

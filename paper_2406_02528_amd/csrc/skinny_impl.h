@@ -92,8 +92,10 @@ __device__ __forceinline__ Words<F> load_words(__amdgpu_buffer_rsrc_t rsrc, uint
   return r;
 }
 
-// F == 1 with NG column groups is also the form for N % 4 != 0: it loads
-// single words and stores single elements.
+// VEC: N % 4 == 0.  Otherwise the word rows start on any dword (buffer loads
+// need dword alignment only and are range-checked dword by dword; columns past
+// N read the next word row or zero and are dropped), and the outputs that
+// cross a row's end are stored one by one.
 template <int FM, int NG, int F, int D, bool VEC, Epilogue EP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void skinny_kernel(const Params p) {
   constexpr int FN = NG * F, BN = 16 * FN;
@@ -300,9 +302,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         int* dst = static_cast<int*>(p.out) + (m0 + tr) * ow + n;
         if constexpr (VEC) {
           if (n < ow) *reinterpret_cast<v4i*>(dst) = v;
+        } else if (n + 3 < ow) {
+          typedef int v4i_dword __attribute__((ext_vector_type(4), aligned(4)));
+          *reinterpret_cast<v4i_dword*>(dst) = v;
         } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
+          for (int r = 0; r < 3; ++r)
             if (n + r < ow) dst[r] = v[r];
         }
       }
@@ -336,9 +341,9 @@ hipError_t dispatch_fn(const ContractArgs& a, int fn, bool tiled, hipStream_t st
     if (a.N % 4 != 0) {
       switch (fn) {
         case 1: return dispatch_d<FM, 1, 1, false, EP>(a, tiled, stream);
-        case 2: return dispatch_d<FM, 2, 1, false, EP>(a, tiled, stream);
-        case 4: return dispatch_d<FM, 4, 1, false, EP>(a, tiled, stream);
-        case 8: return dispatch_d<FM, 8, 1, false, EP>(a, tiled, stream);
+        case 2: return dispatch_d<FM, 1, 2, false, EP>(a, tiled, stream);
+        case 4: return dispatch_d<FM, 1, 4, false, EP>(a, tiled, stream);
+        case 8: return dispatch_d<FM, 2, 4, false, EP>(a, tiled, stream);
         default: return hipErrorInvalidValue;
       }
     }
