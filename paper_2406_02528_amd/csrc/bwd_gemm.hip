@@ -327,7 +327,10 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(2))
         const uint32_t v = *reinterpret_cast<const uint16_t*>(st + r * BK + ((ch ^ a_swz(r)) << 4) + 2 * dc);
         sum += static_cast<double>(__uint_as_float(v << 16));
       }
+      // the lanes exchange through the wave's scratch: its LDS operations
+      // complete in issue order, the fences keep the compiler to that order
       db_red[lane] = sum;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
       if (lane < 8) {
         double t = 0.0;
 #pragma unroll
@@ -335,6 +338,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(2))
         const int n = kt * (BK / 2) + ch * 8 + lane;
         if (n < N) db_part[tm * N + n] = t;
       }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     }
   };
 
