@@ -106,7 +106,9 @@ struct Tiling {
 // dword alignment only and are range-checked dword by dword, so the word rows
 // may start anywhere; a lane's four outputs are stored one by one where they
 // cross the row's end.
-template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4, Epilogue EP, bool RAG = false>
+// BIAS: the dequantised outputs plus aff.bias[n] (the affine epilogue with one
+// segment and no activation, through the staged stores).
+template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4, Epilogue EP, bool RAG = false, bool BIAS = false>
 __global__ __launch_bounds__((Tiling<BM, BN, WM, WN, BK, S, BX4>::kThreads))
 __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
     const int8_t* __restrict__ q, const float* __restrict__ a_scale,
@@ -444,6 +446,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
   // per-element stores.
   constexpr bool kStaged = BX4 && (EP == Epilogue::kDequantF32 || EP == Epilogue::kRawI32);
   static_assert(!RAG || kStaged, "ragged rows leave through the staged stores");
+  static_assert(!BIAS || (kStaged && !RAG && EP == Epilogue::kDequantF32), "the bias is added at the staged stores");
   if constexpr (!kStaged) {
     const int ow = kGlu ? N / 2 : N;  // output row length
     const uint32_t out_bytes = static_cast<uint32_t>(M) * static_cast<uint32_t>(ow) * 4u;
@@ -493,6 +496,14 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
     char* const buf = smem + wave * kBufB;
     const int rr = elane >> 4, qq = elane & 15;  // read-back lane: row rr of 4, column quad qq
     const int n = n0 + wn * WN + 4 * qq;
+    v4f bias = {0.0f, 0.0f, 0.0f, 0.0f};  // of the lane's four columns
+    if constexpr (BIAS) {
+      const __amdgpu_buffer_rsrc_t brsrc =
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(aff.bias), 0, N * 4, kBufferFlags);
+      uint32_t at = 4u * static_cast<uint32_t>(n);
+      if constexpr (kFreshLane) asm volatile("" : "+v"(at));  // not loaded ahead of the k loop
+      bias = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(brsrc, at, 0, 0));
+    }
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm) {
 #pragma unroll
@@ -504,7 +515,11 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const v4i v = *reinterpret_cast<const v4i*>(buf + (4 * i + rr) * kRowB + qq * 16);
+        v4i v = *reinterpret_cast<const v4i*>(buf + (4 * i + rr) * kRowB + qq * 16);
+        if constexpr (BIAS) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) v[r] = __float_as_int(__int_as_float(v[r]) + bias[r]);
+        }
         const int m = m0 + wm * WM + fm * 16 + 4 * i + rr;
         const uint32_t off =
             (m < M && n + (RAG ? 3 : 0) < ow)
@@ -556,7 +571,15 @@ hipError_t launch_cfg(const ContractArgs& a, int64_t m_begin, int64_t m_rows, hi
   const int8_t* q = a.q + m_begin * a.K;
   const float* as = a.a_scale ? a.a_scale + m_begin : nullptr;
   const int32_t* rs = a.q_rowsum + m_begin;
-  if (a.epilogue == Epilogue::kDequantF32)
+  if (a.epilogue == Epilogue::kDequantF32 && a.affine.bias != nullptr) {
+    if constexpr (BX4)
+      hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, BK, S, true, Epilogue::kDequantF32, false, true>), grid, block, 0,
+                         stream, q, as, rs, a.Wpacked, a.w_scale,
+                         static_cast<void*>(static_cast<float*>(a.out) + m_begin * a.N),
+                         static_cast<int>(m_rows), a.K, static_cast<int>(a.N), a.affine);
+    else
+      return hipErrorInvalidValue;
+  } else if (a.epilogue == Epilogue::kDequantF32)
     hipLaunchKernelGGL((gemm_kernel<BM, BN, WM, WN, BK, S, BX4, Epilogue::kDequantF32>), grid, block, 0,
                        stream, q, as, rs, a.Wpacked, a.w_scale,
                        static_cast<void*>(static_cast<float*>(a.out) + m_begin * a.N),
@@ -656,7 +679,16 @@ int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus) {
   return gemm_paired(rows, N, K, cus, ep) ? kPlan128x256Paired : kPlan128x512;
 }
 
-hipError_t launch_gemm(const ContractArgs& a, hipStream_t stream) {
+hipError_t launch_gemm(const ContractArgs& args, hipStream_t stream) {
+  // One segment without an activation is the dequantised output plus a bias:
+  // that goes through the staged stores and the paired tiles, where the
+  // general affine epilogue stores 16 rows x 64 bytes per instruction
+  // (16384 x 1024 x 1024 with a bias: 27 -> 21 us).  The same bits.
+  ContractArgs a = args;
+  if (a.epilogue == Epilogue::kAffineF32 && a.affine.seg == a.N && a.affine.acts == kActIdentity)
+    a.epilogue = Epilogue::kDequantF32;
+  else
+    a.affine.bias = a.epilogue == Epilogue::kAffineF32 ? a.affine.bias : nullptr;
   // 32-bit buffer offsets: a launch covers at most 2^31 - 1 bytes of q, of
   // packed weights and of output; taller problems run in row slices.  The
   // C-ABI layer rejects shapes without a slice before enqueueing anything.

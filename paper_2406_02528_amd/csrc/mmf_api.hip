@@ -925,8 +925,6 @@ int mmf_bitlinear_bwd(const uint16_t* dO, const void* x, int x_is_f32, const flo
     if (mmf::launch_dy(dy, s.dy, stream) != hipSuccess) return MMF_ERR_HIP;
     if (mmf::launch_dx_finish(dx, x, f32, rstd, s_part, s.dy.col_tiles, M, Ki, stream) != hipSuccess)
       return MMF_ERR_HIP;
-    if (dgamma && mmf::launch_col_final(dg_part, s.dy.row_tiles, K, dgamma, stream) != hipSuccess)
-      return MMF_ERR_HIP;
     // dW = dO^T Yq (token range split into parts when the output has few
     // tiles; the last partial round of tiles spread over all CUs otherwise)
     const int64_t S = s.plan.split_all;
@@ -935,7 +933,9 @@ int mmf_bitlinear_bwd(const uint16_t* dO, const void* x, int x_is_f32, const flo
     if (mmf::launch_dw(dOp, q, a_scale, M, s.Np, N, Ki, dw_out, parts, s.plan, stream) != hipSuccess)
       return MMF_ERR_HIP;
     if (S > 1 && mmf::launch_sum_parts(dw_out, S, N * K, dW, stream) != hipSuccess) return MMF_ERR_HIP;
-    if (db && mmf::launch_col_final(db_part, s.dy.row_tiles, N, db, stream) != hipSuccess) return MMF_ERR_HIP;
+    if (mmf::launch_col_final({dg_part, s.dy.row_tiles, K, dgamma}, {db_part, s.dy.row_tiles, N, db}, stream) !=
+        hipSuccess)
+      return MMF_ERR_HIP;
     return MMF_OK;
   });
 }

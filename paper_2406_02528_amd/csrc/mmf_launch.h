@@ -171,8 +171,14 @@ hipError_t launch_mlgru_scan(const float* fcg, const float* h0, float* o, float*
                              int64_t T, int64_t d, float* ws, hipStream_t stream);
 
 // ---- backward (bwd.hip: final sums; bwd_gemm.hip: the two products) ----
-// out[c] = sum over p < nparts of partials[p * cols + c] (fp64, fixed order).
-hipError_t launch_col_final(const double* partials, int64_t nparts, int64_t cols, float* out, hipStream_t stream);
+// out[c] = sum over p < nparts of partials[p * cols + c] (fp64, fixed order);
+// an array with a null `out` is left out.
+struct ColSums {
+  const double* partials;
+  int64_t nparts, cols;
+  float* out;
+};
+hipError_t launch_col_final(const ColSums& a, const ColSums& b, hipStream_t stream);
 // out[i] = sum over s < S of parts[s * n + i], in order, in fp64.
 hipError_t launch_sum_parts(const float* parts, int64_t S, int64_t n, float* out, hipStream_t stream);
 
