@@ -14,20 +14,22 @@ SkinnyPlan skinny_plan(int64_t M, int K, int64_t N, Epilogue ep, int cus) {
   //    cache line each: their weight bytes count twice.
   //  - Tiles of 4 x 8 (and 4 x 4) blocks take the registers of a whole compute
   //    unit: whole rounds, and a quarter more per byte since one workgroup
-  //    cannot cover another's latency.  The others run two per unit.
+  //    cannot cover another's latency (1.45 times for 4 x 16, whose waves read
+  //    each row twice).  The others run two per unit.
   constexpr double kFixed = 60.0;
   const double c = cus > 0 ? cus : 256;
   SkinnyPlan best;
-  for (int fn = 1; fn <= 8; fn *= 2) {
+  for (int fn = 1; fn <= 16; fn *= 2) {
     if (ep == Epilogue::kGluF32 && fn < 2) continue;
     for (int fm = 1; fm <= 4; ++fm) {
+      if (fn == 16 && fm != 4) continue;  // the one form built: smaller ones never measured best
       const int64_t mb = (M + 16 * fm - 1) / (16 * fm), nb = (N + 16 * fn - 1) / (16 * fn);
       if (fm > 1 && 16 * (fm - 1) >= M) continue;  // a block with no row
       const double rows = static_cast<double>(M) / static_cast<double>(mb);
       const double kb = (rows + 16.0 * fn * (fn == 1 ? 0.5 : 0.25)) * K / 1024.0 + kFixed;
       double rounds = static_cast<double>(mb * nb) / c;
       const bool alone = fm * fn >= 16 && fm > 2;
-      if (alone) rounds = 1.25 * static_cast<double>(static_cast<int64_t>(rounds + 0.999999));
+      if (alone) rounds = (fn == 16 ? 1.45 : 1.25) * static_cast<double>(static_cast<int64_t>(rounds + 0.999999));
       if (rounds < 1.0) rounds = 1.0;
       const double cost = rounds * kb;
       if (best.fm == 0 || cost < best.cost) best = {fm, fn, cost};

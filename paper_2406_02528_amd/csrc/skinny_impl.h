@@ -14,7 +14,10 @@
 // through LDS and the k loop has no barrier: every wave loads its fragments
 // from memory into the registers the matrix instruction reads, D steps ahead.
 // The eight partial tiles are then added in LDS (int32, exact) and leave
-// through the epilogue.
+// through the epilogue.  Wide outputs with many rows have more tiles than the
+// chip holds and are bound by the rows every column strip reads again: there
+// WN = 2 halves of the waves take 128 columns each and a quarter of the steps
+// (64 x 256 tiles; 128 x 5120 x 27648: 27.1 -> 24.1 us).
 //
 // Fragments: one k64 step is 4 word rows of the packed weights and 64 bytes
 // of each row of q.  Lane (g, l16) loads bytes 16 g .. 16 g + 15 of row l16 of
@@ -39,8 +42,8 @@
 namespace mmf {
 namespace skinny {
 
-constexpr int kSplit = 8;  // waves per workgroup, each an eighth of the k64 steps
-constexpr int kThreads = kSplit * kWave;
+constexpr int kWaves = 8;  // per workgroup: kWaves / WN shares of the k64 steps
+constexpr int kThreads = kWaves * kWave;
 
 struct Params {
   const int8_t* q;          // [M][K]
@@ -96,9 +99,10 @@ __device__ __forceinline__ Words<F> load_words(__amdgpu_buffer_rsrc_t rsrc, uint
 // need dword alignment only and are range-checked dword by dword; columns past
 // N read the next word row or zero and are dropped), and the outputs that
 // cross a row's end are stored one by one.
-template <int FM, int NG, int F, int D, bool VEC, Epilogue EP>
+template <int FM, int NG, int F, int WN, int D, bool VEC, Epilogue EP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void skinny_kernel(const Params p) {
-  constexpr int FN = NG * F, BN = 16 * FN;
+  constexpr int kSplit = kWaves / WN;
+  constexpr int FN = NG * F, WC = 16 * FN, BN = WC * WN;  // blocks and columns of a wave, columns of the tile
   constexpr int R = rows_per_round(FM, FN);
   constexpr int kStride = BN + 4;  // padded row of a partial tile: conflict-free 16-byte writes of 16 rows
   constexpr int kPart = 16 * R * kStride;
@@ -111,6 +115,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
+  const int kw = wave / WN, nw = wave % WN;  // the wave's share of the steps, its columns
   const int K = p.K, J = K / 16;
   const int64_t N = p.N;
 
@@ -148,15 +153,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 #pragma unroll
   for (int c = 0; c < NG; ++c) {
-    const int64_t col = n0 + c * 16 * F + F * l16;
+    const int64_t col = n0 + nw * WC + c * 16 * F + F * l16;
     b_off[c] = col < N ? static_cast<uint32_t>(g) * row_bytes + 4u * static_cast<uint32_t>(col) : kOutOfRange;
   }
 
   // this wave's share of the k64 steps: [sb, sb + ns)
   const int steps = (J + 3) / 4;
   const int base = steps / kSplit, extra = steps % kSplit;
-  const int sb = wave * base + (wave < extra ? wave : extra);
-  const int ns = base + (wave < extra ? 1 : 0);
+  const int sb = kw * base + (kw < extra ? kw : extra);
+  const int ns = base + (kw < extra ? 1 : 0);
 
   struct Frag {
     v4i a[FM];
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
   for (int f0 = 0; f0 < FM; f0 += R) {
     if (f0 > 0) lds_barrier();
-    int* mine = part + wave * kPart;
+    int* mine = part + kw * kPart + nw * WC;
 #pragma unroll
     for (int fm = f0; fm < f0 + R && fm < FM; ++fm) {
       int* row = mine + ((fm - f0) * 16 + l16) * kStride;
@@ -315,13 +320,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
-template <int FM, int NG, int F, int D, bool VEC, Epilogue EP>
+template <int FM, int NG, int F, int WN, int D, bool VEC, Epilogue EP>
 hipError_t launch_one(const ContractArgs& a, bool tiled, hipStream_t stream) {
-  constexpr int kBM = 16 * FM, kBN = 16 * NG * F;
+  constexpr int kBM = 16 * FM, kBN = 16 * NG * F * WN;
   const int64_t mblocks = (a.M + kBM - 1) / kBM, nblocks = (a.N + kBN - 1) / kBN;
   const Params p{a.q, a.a_scale, a.q_rowsum, a.Wpacked, a.w_scale, a.out, a.M, a.N, a.K,
                  static_cast<int>(mblocks), tiled, a.affine};
-  hipLaunchKernelGGL((skinny_kernel<FM, NG, F, D, VEC, EP>), dim3(static_cast<unsigned>(mblocks * nblocks)),
+  hipLaunchKernelGGL((skinny_kernel<FM, NG, F, WN, D, VEC, EP>), dim3(static_cast<unsigned>(mblocks * nblocks)),
                      dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
@@ -330,9 +335,9 @@ template <int FM, int NG, int F, bool VEC, Epilogue EP>
 hipError_t dispatch_d(const ContractArgs& a, bool tiled, hipStream_t stream) {
   if constexpr (skinny_deep(FM, NG * F)) {
     // more than two steps per wave
-    if (a.K > 2 * 64 * kSplit) return launch_one<FM, NG, F, 4, VEC, EP>(a, tiled, stream);
+    if (a.K > 2 * 64 * kWaves) return launch_one<FM, NG, F, 1, 4, VEC, EP>(a, tiled, stream);
   }
-  return launch_one<FM, NG, F, 2, VEC, EP>(a, tiled, stream);
+  return launch_one<FM, NG, F, 1, 2, VEC, EP>(a, tiled, stream);
 }
 
 template <int FM, Epilogue EP>
@@ -344,6 +349,9 @@ hipError_t dispatch_fn(const ContractArgs& a, int fn, bool tiled, hipStream_t st
         case 2: return dispatch_d<FM, 1, 2, false, EP>(a, tiled, stream);
         case 4: return dispatch_d<FM, 1, 4, false, EP>(a, tiled, stream);
         case 8: return dispatch_d<FM, 2, 4, false, EP>(a, tiled, stream);
+        case 16:
+          if constexpr (FM == 4) return launch_one<FM, 2, 4, 2, 2, false, EP>(a, tiled, stream);
+          return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
       }
     }
@@ -356,6 +364,9 @@ hipError_t dispatch_fn(const ContractArgs& a, int fn, bool tiled, hipStream_t st
     case 2: return dispatch_d<FM, 1, 2, true, EP>(a, tiled, stream);
     case 4: return dispatch_d<FM, 1, 4, true, EP>(a, tiled, stream);
     case 8: return dispatch_d<FM, 2, 4, true, EP>(a, tiled, stream);
+    case 16:
+      if constexpr (FM == 4) return launch_one<FM, 2, 4, 2, 2, true, EP>(a, tiled, stream);
+      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

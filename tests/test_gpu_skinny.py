@@ -55,6 +55,10 @@ SHAPES = [(17, 16, 100), (17, 1040, 1000), (31, 2064, 6000), (33, 2096, 2044), (
           (400, 112, 48), (1, 16400, 96), (5, 13824, 324), (16, 13824, 5120), (33, 1024, 5)]
 
 
+# the 64 x 256 tile (two column halves, four shares of K), ragged in each dimension
+SHAPES += [(100, 2064, 27000), (127, 1040, 27001), (250, 4112, 15300)]
+
+
 @pytest.mark.parametrize("M,K,N", SHAPES)
 @pytest.mark.parametrize("f32", [False, True])
 def test_forward_equals_the_gemm_path(mmf, M, K, N, f32):
@@ -91,7 +95,7 @@ def test_integer_sums_from_rows_of_q(mmf, M, K, N):
     assert torch.equal(acc.cpu().to(torch.int64), q.to(torch.int64) @ t.t())
 
 
-@pytest.mark.parametrize("M,K,L", [(17, 16, 16), (33, 1040, 2832), (45, 2048, 5632), (200, 2064, 528), (128, 5120, 1744)])
+@pytest.mark.parametrize("M,K,L", [(17, 16, 16), (33, 1040, 2832), (45, 2048, 5632), (200, 2064, 528), (128, 5120, 1744), (120, 1040, 13824)])
 def test_glu_equals_the_gemm_path(mmf, M, K, L):
     print(f"glu M={M} K={K} L={L}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(5)
