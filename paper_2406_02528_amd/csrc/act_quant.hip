@@ -6,6 +6,7 @@
 // absmax of the normalised values) are reduced across the row's lanes.
 #include "mmf_device.h"
 #include "mmf_launch.h"
+#include "q_layout.h"
 
 namespace mmf {
 namespace {
@@ -142,9 +143,7 @@ __global__ __launch_bounds__(kWave* block_waves(W)) void act_quant_kernel(
   const int trows = static_cast<int>(M - t16 < 16 ? M - t16 : 16);
   int8_t* const qr = q + (TILED ? t16 : srow) * K;
   auto q_at = [&](int k) -> int8_t* {
-    if constexpr (!TILED) return qr + k;
-    const int s = k / 64, piece = K - 64 * s < 64 ? K - 64 * s : 64;
-    return qr + static_cast<int64_t>(64 * s) * trows + static_cast<int>(srow - t16) * piece + k % 64;
+    return qr + (TILED ? tiled_q_piece(static_cast<int>(srow - t16), trows, k, K) : k);
   };
 
   if constexpr (VPL > 0) {
@@ -157,22 +156,21 @@ __global__ __launch_bounds__(kWave* block_waves(W)) void act_quant_kernel(
     typename V::Raw raw[VPL];
     float4 gv[VPL][E / 4];
     if constexpr (MLGRU) {
-      // f, c and g side by side in the row of fcg; the state through a
-      // resource of size 0 when there is none
+      // f, c and g side by side in the row of fcg (a row past M reads the
+      // first one's); the state through a resource of size 0 when there is none
       const __amdgpu_buffer_rsrc_t frsrc = __builtin_amdgcn_make_buffer_rsrc(
-          const_cast<float*>(step.fcg + srow * 3 * K), 0, live ? 3 * K * 4 : 0, kBufferFlags);
+          const_cast<float*>(step.fcg + srow * 3 * K), 0, static_cast<int>(gate_row(0, K).bytes), kBufferFlags);
       const __amdgpu_buffer_rsrc_t hrsrc = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<float*>(step.h_in + (step.h_in != nullptr ? srow * K : 0)), 0,
           live && step.h_in != nullptr ? K * 4 : 0, kBufferFlags);
       float4 fv[VPL], cv[VPL], hv[VPL];
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {
-        const int v = rl + W * kWave * i;
-        const uint32_t off = v < nvec ? static_cast<uint32_t>(v * 16) : 0x80000000u;
-        fv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, off, 0, 0));
-        cv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, off, K * 4, 0));
-        raw[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, off, 2 * K * 4, 0));
-        hv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(hrsrc, off, 0, 0));
+        const GateRow at = gate_row(rl + W * kWave * i, K);
+        fv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, at.lane, at.f, 0));
+        cv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, at.lane, at.c, 0));
+        raw[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(frsrc, at.lane, at.g, 0));
+        hv[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(hrsrc, at.lane, 0, 0));
       }
 #pragma unroll
       for (int i = 0; i < VPL; ++i) {

@@ -6,20 +6,9 @@
 
 namespace mmf {
 
-// The TiledQ layout of q (M * K bytes, as the rows): row blocks of 16 rows at
-// 16 b K; in a block of mr rows (16, or M % 16 in the last) the 64-byte pieces
-// of step s = k / 64 at 64 s mr, row r's at 64 r within them (K % 64 bytes per
-// row in a last step of less than 64).  Byte offset of row m, feature k:
-__host__ __device__ inline int64_t tiled_q_offset(int64_t m, int k, int64_t M, int K) {
-  const int64_t b = m / 16, r = m % 16;
-  const int64_t mr = M - 16 * b < 16 ? M - 16 * b : 16;
-  const int s = k / 64, piece = K - 64 * s < 64 ? K - 64 * s : 64;
-  return 16 * b * K + 64 * s * mr + r * piece + k % 64;
-}
-
 // RMSNorm + absmax int8 quantisation of M rows of K features (K % 16 == 0);
 // rstd (optional) receives each row's 1/sqrt(mean x^2 + eps); `tiled` writes q
-// in the TiledQ layout instead of rows.
+// in the TiledQ layout (q_layout.h) instead of rows.
 hipError_t launch_act_quant(const void* x, bool x_is_f32, const float* gamma, int8_t* q,
                             float* a_scale, int32_t* q_rowsum, int64_t M, int K,
                             hipStream_t stream, float* rstd = nullptr, bool tiled = false);

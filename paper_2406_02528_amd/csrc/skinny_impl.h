@@ -23,13 +23,14 @@
 // of each row of q.  Lane (g, l16) loads bytes 16 g .. 16 g + 15 of row l16 of
 // each 16-row block (one 16-byte load), and the words of word row 4 s + g of
 // its F consecutive columns F l16 .. F l16 + F - 1 in each of the NG column
-// groups (one 4-, 8- or 16-byte load).  Rows past M and word rows past K / 16
-// fall outside the buffer resources and read as zero.
+// groups (one 4-, 8- or 16-byte load).  Word rows past K / 16 fall outside the
+// buffer resource and read as zero, so what the row fragments hold there (and
+// in rows past M, whose sums are dropped) does not matter.
 //
 // q comes in one of two layouts: rows ([M][K], the public one), or tiled as
 // the library's own act-quant launch writes it for this kernel, each 16-row
 // block's 64-byte pieces of a k64 step next to each other (TiledQ in
-// mmf_launch.h), so that a fragment is 1 KB of consecutive memory instead of
+// q_layout.h), so that a fragment is 1 KB of consecutive memory instead of
 // 16 half cache lines K bytes apart: with K a multiple of 1024 those fall on
 // few L2 channels.  Measured from rows -> tiled, us: 48 x 5632 x 2048
 // 7.7 -> 5.3, 128 x 5120 x 15360 20.1 -> 15.9, 128 x 13824 x 5120
@@ -38,6 +39,7 @@
 #include "gemm_common.h"
 #include "mmf_device.h"
 #include "mmf_launch.h"
+#include "q_layout.h"
 
 namespace mmf {
 namespace skinny {
@@ -139,18 +141,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       kBufferFlags);
   const uint32_t row_bytes = 4u * static_cast<uint32_t>(N);
   // A fragment of block fm and step s: a lane offset (another one in a last
-  // step of less than 64 bytes per row, whose tiled pieces are shorter) and a
-  // wave-uniform one, 16 fm K + s a_step (the block's rows x 64 when tiled).
-  const uint32_t tail = static_cast<uint32_t>(K % 64);
-  const uint32_t a_lane = static_cast<uint32_t>(l16) * (p.tiled ? 64u : static_cast<uint32_t>(K)) + 16u * g;
-  const uint32_t a_lane_tail = p.tiled && tail != 0 ? static_cast<uint32_t>(l16) * tail + 16u * g : a_lane;
-  uint32_t a_base[FM], a_step[FM], b_off[NG];
+  // step of less than 64 bytes per row) and a wave-uniform one, both inside
+  // the resource or past it by the lane offset alone (q_layout.h).
+  const uint32_t a_lane = q_lane(l16, g, K, p.tiled, false), a_lane_last = q_lane(l16, g, K, p.tiled, true);
+  QBlock a_at[FM];
+  uint32_t b_off[NG];
 #pragma unroll
-  for (int fm = 0; fm < FM; ++fm) {
-    const int live = rows - 16 * fm < 16 ? rows - 16 * fm : 16;  // rows of the block (<= 0: all reads are past q)
-    a_base[fm] = static_cast<uint32_t>(fm * 16) * static_cast<uint32_t>(K);
-    a_step[fm] = p.tiled && live > 0 ? static_cast<uint32_t>(64 * live) : 64u;
-  }
+  for (int fm = 0; fm < FM; ++fm) a_at[fm] = q_block(rows, fm, K, p.tiled);
 #pragma unroll
   for (int c = 0; c < NG; ++c) {
     const int64_t col = n0 + nw * WC + c * 16 * F + F * l16;
@@ -172,11 +169,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const uint32_t bs = static_cast<uint32_t>(s) * 4u * row_bytes;
 #pragma unroll
     for (int c = 0; c < NG; ++c) f.b[c] = load_words<F>(brsrc, b_off[c], bs);
-    const uint32_t al = s == steps - 1 ? a_lane_tail : a_lane;
+    const uint32_t al = s == steps - 1 ? a_lane_last : a_lane;
 #pragma unroll
     for (int fm = 0; fm < FM; ++fm)
       f.a[fm] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(
-                                            arsrc, al, a_base[fm] + static_cast<uint32_t>(s) * a_step[fm], 0));
+                                            arsrc, al, a_at[fm].base + static_cast<uint32_t>(s) * a_at[fm].step, 0));
   };
   v4i acc[FM][FN];
 #pragma unroll
