@@ -914,8 +914,8 @@ DyPlan bwd_dy_plan(int64_t M, int64_t K, int cus) {
   const double t_small = n <= 6 ? kSmall[n] : 0.32 * static_cast<double>(n);
   DyPlan p;
   if (t_small <= static_cast<double>((wide + c - 1) / c)) {
-    p.bm = 64;
-    p.bn = 256;
+    p.bm = kDyMinRows;
+    p.bn = kDyMinCols;
   }
   p.row_tiles = (M + p.bm - 1) / p.bm;
   p.col_tiles = (K + p.bn - 1) / p.bn;
@@ -946,7 +946,7 @@ static hipError_t launch_dy_tile(const DyArgs& a, int64_t mb, int64_t rows, hipS
 
 template <typename XT>
 static hipError_t launch_dy_x(const DyArgs& a, const DyPlan& p, int64_t mb, int64_t rows, hipStream_t stream) {
-  if (p.bm == 64) return launch_dy_tile<XT, DyTile<64, 256>>(a, mb, rows, stream);
+  if (p.bm == kDyMinRows) return launch_dy_tile<XT, DyTile<kDyMinRows, kDyMinCols>>(a, mb, rows, stream);
   return launch_dy_tile<XT, DyTile<128, 512>>(a, mb, rows, stream);
 }
 

@@ -419,12 +419,14 @@ BwdScratch bwd_scratch(int64_t M, int64_t K, int64_t N) {
   s.dop_off = round_up(static_cast<size_t>(mmf::bwd_nmajor_words(N, K)) * 4, kScratchAlign);
   const size_t dop = s.Np != N ? static_cast<size_t>(M) * static_cast<size_t>(s.Np) * 2 : 0;
   s.spart_off = s.dop_off + round_up(dop, kScratchAlign);
-  s.dgpart_off = s.spart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.col_tiles * M),
-                                        kScratchAlign);
-  s.dbpart_off = s.dgpart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.row_tiles * K),
-                                          kScratchAlign);
-  s.dw_off = s.dbpart_off + round_up(sizeof(double) * static_cast<size_t>(s.dy.row_tiles * N),
-                                      kScratchAlign);
+  // The dY partials of the smallest tile whatever the plan: the size then
+  // never falls as M grows, so the workspace of the largest batch serves
+  // every smaller one.
+  const int64_t row_tiles = (M + mmf::kDyMinRows - 1) / mmf::kDyMinRows;
+  const int64_t col_tiles = (K + mmf::kDyMinCols - 1) / mmf::kDyMinCols;
+  s.dgpart_off = s.spart_off + round_up(sizeof(double) * static_cast<size_t>(col_tiles * M), kScratchAlign);
+  s.dbpart_off = s.dgpart_off + round_up(sizeof(double) * static_cast<size_t>(row_tiles * K), kScratchAlign);
+  s.dw_off = s.dbpart_off + round_up(sizeof(double) * static_cast<size_t>(row_tiles * N), kScratchAlign);
   const int64_t S = s.plan.split_all;
   s.parts_off = s.dw_off + (S > 1 ? round_up(sizeof(float) * static_cast<size_t>(S * N * K), kScratchAlign) : 0);
   s.total = s.parts_off + round_up(mmf::bwd_dw_parts_bytes(s.plan), kScratchAlign);

@@ -184,6 +184,7 @@ hipError_t launch_pad_rows(const uint16_t* src, int64_t M, int64_t N, int64_t N8
 // [row_tiles][K] and db_part [row_tiles][N] (the column sums of dO per row
 // tile, for db), on bm x bn tiles.  bwd_dy_row_slice(Np, K) == 0: shape not
 // supported (32-bit offsets).
+constexpr int kDyMinRows = 64, kDyMinCols = 256;  // the smallest tile
 struct DyPlan {
   int bm = 128, bn = 512;
   int64_t row_tiles = 0, col_tiles = 0;

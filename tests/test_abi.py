@@ -343,6 +343,15 @@ def test_backward_shapes_past_its_offsets_are_rejected_up_front(mmf):
     assert lib.mmf_bitlinear_bwd_workspace_bytes(64, 2048, (1 << 18) - 1) > 0
 
 
+@pytest.mark.parametrize("K,N,M", [(1024, 1024, 16384), (2048, 11264, 8192), (2048, 2048, 8192), (1024, 4096, 16384),
+                                   (2288, 3998, 4096), (2048, 5632, 16384), (1024, 1001, 16384), (4096, 1024, 8192)])
+def test_backward_workspace_of_a_batch_serves_smaller_ones(mmf, K, N, M):
+    """A last, smaller batch runs in the workspace of the full one, whatever
+    tiles either takes."""
+    full = mmf._lib.mmf_bitlinear_bwd_workspace_bytes(M, K, N)
+    assert not [m for m in range(1, M) if mmf._lib.mmf_bitlinear_bwd_workspace_bytes(m, K, N) > full]
+
+
 def test_noalloc_argument_checks(mmf):
     """The forward without allocation: the same checks as the forward, and
     scratch needs past its static array rejected before anything is
