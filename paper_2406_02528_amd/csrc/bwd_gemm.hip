@@ -104,36 +104,40 @@ __global__ __launch_bounds__(kBlock) void pack_nmajor_kernel(const uint32_t* __r
 }
 
 // dO rows padded with zeros to a multiple of 8 columns (16-byte chunks): one
-// row per blockIdx.x, one 16-byte chunk per thread.  Rows of odd N start on 2
+// 16-byte chunk per thread, a row per blockIdx.x and, past kPadGridRows rows,
+// every kPadGridRows-th one after it (a launch holds fewer than 2^32 threads
+// in x).  Rows of odd N start on 2
 // bytes, so a chunk inside the row is read as the five dwords that cover it
 // and shifted; the chunk at the row's end element by element.  (One element
 // per thread with a 64-bit division each took 18 us for 1937 x 3998.)
+constexpr int64_t kPadGridRows = int64_t(1) << 22;
 __global__ __launch_bounds__(kBlock) void pad_rows_kernel(const uint16_t* __restrict__ src, int64_t M, int N, int N8,
                                                           uint16_t* __restrict__ dst) {
-  const int64_t m = blockIdx.x;
   const int c = (blockIdx.y * kBlock + threadIdx.x) * 8;
   if (c >= N8) return;
-  const uint16_t* s = src + m * N;
-  uint32_t w[5];
-  if (c + 9 < N) {
-    // elements c - 1 .. c + 8 or c .. c + 9: inside the array, since c - 1 of
-    // the first row's first chunk is never read (the array is aligned)
-    const uintptr_t at = reinterpret_cast<uintptr_t>(s + c);
-    const uint32_t* p = reinterpret_cast<const uint32_t*>(at & ~uintptr_t(3));
-    const uint32_t sh = (at & 2) ? 16 : 0;
+  for (int64_t m = blockIdx.x; m < M; m += kPadGridRows) {
+    const uint16_t* s = src + m * N;
+    uint32_t w[5];
+    if (c + 9 < N) {
+      // elements c - 1 .. c + 8 or c .. c + 9: inside the array, since c - 1 of
+      // the first row's first chunk is never read (the array is aligned)
+      const uintptr_t at = reinterpret_cast<uintptr_t>(s + c);
+      const uint32_t* p = reinterpret_cast<const uint32_t*>(at & ~uintptr_t(3));
+      const uint32_t sh = (at & 2) ? 16 : 0;
 #pragma unroll
-    for (int i = 0; i < 5; ++i) w[i] = p[i];
+      for (int i = 0; i < 5; ++i) w[i] = p[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], sh);
-  } else {
+      for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_alignbit(w[i + 1], w[i], sh);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t lo = c + 2 * i < N ? s[c + 2 * i] : 0u;
-      const uint32_t hi = c + 2 * i + 1 < N ? s[c + 2 * i + 1] : 0u;
-      w[i] = lo | (hi << 16);
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t lo = c + 2 * i < N ? s[c + 2 * i] : 0u;
+        const uint32_t hi = c + 2 * i + 1 < N ? s[c + 2 * i + 1] : 0u;
+        w[i] = lo | (hi << 16);
+      }
     }
+    *reinterpret_cast<uint4*>(dst + m * N8 + c) = make_uint4(w[0], w[1], w[2], w[3]);
   }
-  *reinterpret_cast<uint4*>(dst + m * N8 + c) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
 // ---------------------------------------------------------------------------
@@ -891,7 +895,9 @@ hipError_t launch_pack_nmajor(const uint32_t* Wpacked, int64_t N, int64_t Np, in
 
 hipError_t launch_pad_rows(const uint16_t* src, int64_t M, int64_t N, int64_t N8, uint16_t* dst, hipStream_t stream) {
   if (M * N8 == 0) return hipSuccess;
-  hipLaunchKernelGGL(pad_rows_kernel, dim3(static_cast<unsigned>(M), static_cast<unsigned>((N8 / 8 + kBlock - 1) / kBlock)),
+  hipLaunchKernelGGL(pad_rows_kernel,
+                     dim3(static_cast<unsigned>(M < kPadGridRows ? M : kPadGridRows),
+                          static_cast<unsigned>((N8 / 8 + kBlock - 1) / kBlock)),
                      dim3(kBlock), 0, stream, src, M, static_cast<int>(N), static_cast<int>(N8), dst);
   return hipGetLastError();
 }

@@ -59,3 +59,32 @@ def test_odd_widths_equal_the_widened_matrix(mmf, M, K, N, plan):  # noqa: F811
 def test_dy_tiles(mmf, M, K, N, f32_x, with_gamma):  # noqa: F811
     print(f"dY M={M} K={K} N={N}", flush=True)
     run_bwd(mmf, M, K, N, f32_x, with_gamma, seed=11)
+
+
+# More rows than pad_rows_kernel's grid: each workgroup then pads several.
+def test_padding_of_very_many_rows(mmf):  # noqa: F811
+    M, K, N = (1 << 22) + 9, 16, 3
+    print(f"pad M={M} K={K} N={N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    dO = torch.randn(M, N, generator=g, device="cuda").bfloat16()
+    W = torch.randn(N, K, generator=g, device="cuda") * 0.02
+    e = lambda *s, t=torch.float32: torch.empty(s, dtype=t, device="cuda")  # noqa: E731
+    y, Wp, ws, q, a, r = e(M, N), e(1, N, t=torch.int32), e(1), e(M, K, t=torch.int8), e(M), e(M)
+    mmf.mmf_bitlinear_train_fwd(x, None, W, None, y, Wp, ws, q, a, r)
+    dx, dW, db = e(M, K).fill_(float("nan")), e(N, K), e(N)
+    mmf.mmf_bitlinear_bwd(dO, x, None, r, q, a, Wp, ws, dx, dW, db, None)
+    t = torch.clamp(torch.round(W.cpu() * (1.0 / ws.cpu())), -1, 1).double().cuda()
+    xd, rd = x.double(), r.double()[:, None]
+    def parts(d, t, x):  # the two terms of dx
+        dY = (d @ t) * ws.double()
+        return rd * dY, x * (dY * x).sum(1, keepdim=True) * rd ** 3 / K
+
+    p1, p2 = parts(dO.double(), t, xd)
+    # fp32: a sum of three exact products (rounded relative to the sum of their
+    # magnitudes), its factors and the difference, fewer than 16 roundings of
+    # 2^-24: 1e-6 of the terms formed from magnitudes
+    b1, b2 = parts(dO.double().abs(), t.abs(), xd.abs())
+    assert ((dx.double() - (p1 - p2)).abs() <= 1e-6 * (b1 + b2)).all()
+    ref = dO.double().sum(0)  # fp64 on both sides, rounded once: 2^-24, and 2^-52 per addend
+    assert ((db.double() - ref).abs() <= 1e-7 * ref.abs() + 1e-15 * dO.double().abs().sum(0)).all()
