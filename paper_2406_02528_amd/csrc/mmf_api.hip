@@ -43,24 +43,27 @@ FwdScratch fwd_scratch(int64_t M, int64_t K) {
   return s;
 }
 
-// Automatic choice: up to decode_max_tokens(K) tokens run as decode launches
-// of at most 16 tokens each, when the decode kernel takes such a slice (its
-// LDS holds q of 16 tokens up to K = 7680); more go to the MFMA kernel, whose
-// time at a small M is one tile's k loop (latency-bound, ~0.6-0.9 us per 128
-// of K).  Measured forward calls from x, decode slices at 16 / 32 / 48 / 64
-// tokens against the MFMA kernel at 16-128 tokens: K = 1024, N = 4096: 5.0 /
-// 9.5 / 13.9 / 18.1 us against 10.2-11.8; K = 2048, N = 6144: 6.7 / 12.7 /
-// 18.6 / 24.5 against 15.2-17.2; K = 4096, N = 11008: 9.2 / 14.1 / 18.8 /
-// 23.6 against 24.0-26.4; K = 5120, N = 15360: 11.5 / 16.7 / 21.6 / 26.8
-// against 35.2-37.3.  So 32 tokens at K <= 2048, 64 beyond.  MMF_PATH_GEMV
-// forces the decode kernels for every M (slices they cannot hold then go to
-// the gemv kernel, which reads q from global memory); MMF_PATH_GEMM forces
-// the MFMA kernel.
+// The kernel selection a call runs under.  It is process-wide and may change
+// on another thread, so an entry point reads it once and every later decision
+// of the call (checks, scratch size, kernels) is made from that value.
+int current_path() { return g_path.load(std::memory_order_relaxed); }
+
+// Whether rows run as decode launches of at most 16 tokens each: on the
+// automatic path up to decode_max_tokens(K) tokens, when the decode kernel
+// takes such a slice (its LDS holds q of 16 tokens up to K = 7680).  Beyond 16
+// tokens that is the form without scratch (route_from_x takes the K-split
+// kernel where there is some); it was set against the tiled MFMA kernel, whose
+// time at a small M is one tile's k loop (forward calls from x, slices at 16 /
+// 32 / 48 / 64 tokens against the tiled kernel at 16-128 tokens: K = 2048, N =
+// 6144: 6.7 / 12.7 / 18.6 / 24.5 us against 15.2-17.2; K = 5120, N = 15360:
+// 11.5 / 16.7 / 21.6 / 26.8 against 35.2-37.3).  MMF_PATH_GEMV forces the
+// decode kernels for every M (slices they cannot hold then go to the gemv
+// kernel, which reads q from global memory); MMF_PATH_GEMM forces the tiled
+// MFMA kernel.
 int64_t decode_max_tokens(int64_t K) { return K <= 2048 ? 32 : 64; }
-bool use_decode(int64_t M, int64_t K, int64_t N, bool from_x, bool x_is_f32) {
-  const int p = g_path.load(std::memory_order_relaxed);
-  if (p == MMF_PATH_GEMV) return true;
-  if (p == MMF_PATH_GEMM) return false;
+bool use_decode(int path, int64_t M, int64_t K, int64_t N, bool from_x, bool x_is_f32) {
+  if (path == MMF_PATH_GEMV) return true;
+  if (path == MMF_PATH_GEMM) return false;
   if (M > decode_max_tokens(K)) return false;
   return mmf::decode_fits(M < kDecodeMaxTokens ? M : kDecodeMaxTokens, static_cast<int>(K), N, from_x,
                           x_is_f32);
@@ -68,9 +71,8 @@ bool use_decode(int64_t M, int64_t K, int64_t N, bool from_x, bool x_is_f32) {
 
 // Whether the automatic path contracts these rows with K split over the waves
 // of a workgroup (skinny.hip).
-bool use_skinny(int64_t M, int64_t K, int64_t N, mmf::Epilogue ep, bool tiled) {
-  return g_path.load(std::memory_order_relaxed) == MMF_PATH_AUTO &&
-         mmf::skinny_takes(M, static_cast<int>(K), N, ep, tiled, mmf::device_cus());
+bool use_skinny(int path, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep, bool tiled) {
+  return path == MMF_PATH_AUTO && mmf::skinny_takes(M, static_cast<int>(K), N, ep, tiled, mmf::device_cus());
 }
 
 // Whether the decode kernel contracts these rows of q in one launch (its
@@ -82,8 +84,8 @@ bool one_decode_launch(int64_t M, int64_t K, int64_t N, mmf::Epilogue ep) {
 
 // The MFMA contraction from rows of q: the K-split kernel for few rows, else
 // the tiled GEMM kernel.
-hipError_t contract_mfma(const mmf::ContractArgs& a, hipStream_t stream) {
-  if (use_skinny(a.M, a.K, a.N, a.epilogue, false)) return mmf::launch_skinny(a, false, stream);
+hipError_t contract_mfma(int path, const mmf::ContractArgs& a, hipStream_t stream) {
+  if (use_skinny(path, a.M, a.K, a.N, a.epilogue, false)) return mmf::launch_skinny(a, false, stream);
   return mmf::launch_gemm(a, stream);
 }
 
@@ -91,10 +93,10 @@ hipError_t contract_mfma(const mmf::ContractArgs& a, hipStream_t stream) {
 // it fits; more take the MFMA kernels.  On the forced decode path every slice
 // of 16 tokens runs as a decode launch, those whose q does not fit LDS reading
 // it from global memory.
-hipError_t contract(const mmf::ContractArgs& a, hipStream_t stream) {
-  if (!one_decode_launch(a.M, a.K, a.N, a.epilogue) && use_skinny(a.M, a.K, a.N, a.epilogue, false))
+hipError_t contract(int path, const mmf::ContractArgs& a, hipStream_t stream) {
+  if (!one_decode_launch(a.M, a.K, a.N, a.epilogue) && use_skinny(path, a.M, a.K, a.N, a.epilogue, false))
     return mmf::launch_skinny(a, false, stream);
-  if (!use_decode(a.M, a.K, a.N, false, false)) return mmf::launch_gemm(a, stream);
+  if (!use_decode(path, a.M, a.K, a.N, false, false)) return mmf::launch_gemm(a, stream);
   for (int64_t m0 = 0; m0 < a.M; m0 += kDecodeMaxTokens) {
     const int64_t mt = a.M - m0 < kDecodeMaxTokens ? a.M - m0 : kDecodeMaxTokens;
     const bool raw = a.epilogue == mmf::Epilogue::kRawI32;
@@ -116,21 +118,27 @@ hipError_t contract(const mmf::ContractArgs& a, hipStream_t stream) {
   return hipSuccess;
 }
 
-// The whole forward runs as fused decode launches (no scratch) when every
-// slice of at most 16 tokens fits the fused kernel.
-bool fused_decode(int64_t M, int64_t K, int64_t N, bool x_is_f32) {
-  if (!use_decode(M, K, N, true, x_is_f32)) return false;
+// The whole forward can run as fused decode launches (no scratch): every slice
+// of at most 16 tokens fits the fused kernel.
+bool fused_decode(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32) {
+  if (!use_decode(path, M, K, N, true, x_is_f32)) return false;
   const int64_t mt = M < kDecodeMaxTokens ? M : kDecodeMaxTokens;
   return mmf::decode_fits(mt, static_cast<int>(K), N, true, x_is_f32);
 }
 
-// Whether a forward from x runs as act-quant (q tiled, into scratch) and the
-// K-split contraction although fused decode launches would take it: one fused
-// launch up to 16 tokens, but its row stage repeats in every workgroup and
-// each further 16 tokens stream the weights again.  Measured forward calls
-// from bf16 x, fused slices -> act-quant + K-split: see skinny_takes.
-bool prefers_skinny(int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep) {
-  return (M > kDecodeMaxTokens || !fused_decode(M, K, N, x_is_f32)) && use_skinny(M, K, N, ep, true);
+// How a forward from x runs: fused decode launches of 16 tokens, or act-quant
+// into scratch with q tiled for the K-split kernel behind it, or with rows of
+// q for the others.  More than 16 tokens prefer the K-split kernel where there
+// is scratch: the fused kernel's row stage repeats in every workgroup and each
+// further 16 tokens stream the weights again (forward calls from bf16 x,
+// slices -> act-quant + K-split, us: 17 x 1024 x 6144 8.0 -> 5.9,
+// 32 x 2048 x 6144 12.9 -> 6.4, 64 x 5120 x 27648 49.0 -> 20.4).
+enum class Route { kFusedDecode, kTiledQ, kRows };
+Route route_from_x(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep, bool scratch) {
+  const bool fused = fused_decode(path, M, K, N, x_is_f32);
+  if (fused && (M <= kDecodeMaxTokens || !scratch)) return Route::kFusedDecode;
+  if (!one_decode_launch(M, K, N, ep) && use_skinny(path, M, K, N, ep, true)) return Route::kTiledQ;
+  return fused ? Route::kFusedDecode : Route::kRows;
 }
 
 // Whether work on `stream` is being captured into a graph (or that cannot be
@@ -141,29 +149,34 @@ bool capturing(hipStream_t stream) {
   return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
-// Scratch a forward without caller workspace allocates: none when it runs as
-// fused decode launches.
-size_t fwd_need(int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep, hipStream_t stream) {
-  if (fused_decode(M, K, N, x_is_f32) && (!prefers_skinny(M, K, N, x_is_f32, ep) || capturing(stream))) return 0;
-  return fwd_scratch(M, K).total;
-}
-
-// act-quant into `scratch` and the contraction behind it: tiled q and the
-// K-split kernel for few rows, rows of q and `contract_rows` otherwise.
-template <class C>
-hipError_t quant_contract(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
-                          const float* w_scales, void* out, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep,
-                          const mmf::Affine& aff, char* scratch, hipStream_t stream, C&& contract_rows) {
+// A forward from x on `route` (scratch: fwd_scratch(M, K), not used by fused
+// decode launches): x -> RMSNorm + quantisation -> the contraction with
+// epilogue `ep` into out.
+int run_from_x(int path, Route route, const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
+               const float* w_scales, float* out, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep,
+               const mmf::Affine& aff, char* scratch, hipStream_t stream) {
+  const int Ki = static_cast<int>(K);
+  if (route == Route::kFusedDecode) {
+    const size_t xsz = x_is_f32 ? 4 : 2;
+    const int64_t ow = ep == mmf::Epilogue::kGluF32 ? N / 2 : N;
+    for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
+      const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
+      const mmf::DecodeArgs d{static_cast<const char*>(x) + m0 * K * xsz, x_is_f32, gamma, nullptr, nullptr, nullptr,
+                              Wpacked, w_scales, out + m0 * ow, mt, Ki, N, ep, aff};
+      if (mmf::launch_decode(d, stream) != hipSuccess) return MMF_ERR_HIP;
+    }
+    return MMF_OK;
+  }
   const FwdScratch s = fwd_scratch(M, K);
   int8_t* q = reinterpret_cast<int8_t*>(scratch + s.q_off);
   float* a_scale = reinterpret_cast<float*>(scratch + s.a_off);
   int32_t* rowsum = reinterpret_cast<int32_t*>(scratch + s.r_off);
-  const bool tiled = !one_decode_launch(M, K, N, ep) && use_skinny(M, K, N, ep, true);
-  const hipError_t e = mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M, static_cast<int>(K), stream,
-                                             nullptr, tiled);
-  if (e != hipSuccess) return e;
-  const mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scales, out, M, static_cast<int>(K), N, ep, aff};
-  return tiled ? mmf::launch_skinny(a, true, stream) : contract_rows(a, stream);
+  const bool tiled = route == Route::kTiledQ;
+  if (mmf::launch_act_quant(x, x_is_f32, gamma, q, a_scale, rowsum, M, Ki, stream, nullptr, tiled) != hipSuccess)
+    return MMF_ERR_HIP;
+  const mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scales, out, M, Ki, N, ep, aff};
+  if (tiled) return hip_status(mmf::launch_skinny(a, true, stream));
+  return hip_status(ep == mmf::Epilogue::kDequantF32 ? contract(path, a, stream) : contract_mfma(path, a, stream));
 }
 
 // Shape limits of the kernels a call will run, checked before anything is
@@ -175,52 +188,27 @@ hipError_t quant_contract(const void* x, bool x_is_f32, const float* gamma, cons
 int check_gemm(int64_t K, int64_t N) {
   return mmf::gemm_row_slice(K, N) > 0 ? MMF_OK : MMF_ERR_SHAPE;
 }
-int check_contract(int64_t M, int64_t K, int64_t N) {
-  if (M == 0 || N == 0 || use_decode(M, K, N, false, false)) return MMF_OK;
+int check_contract(int path, int64_t M, int64_t K, int64_t N) {
+  if (M == 0 || N == 0 || use_decode(path, M, K, N, false, false)) return MMF_OK;
   return check_gemm(K, N);
 }
-int check_from_x(int64_t M, int64_t K, int64_t N, bool x_is_f32, bool gemm_only) {
-  if (M == 0 || N == 0 || fused_decode(M, K, N, x_is_f32)) return MMF_OK;
-  return gemm_only ? check_gemm(K, N) : check_contract(M, K, N);
+int check_from_x(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32, bool gemm_only) {
+  if (M == 0 || N == 0 || fused_decode(path, M, K, N, x_is_f32)) return MMF_OK;
+  return gemm_only ? check_gemm(K, N) : check_contract(path, M, K, N);
 }
 int check_dtype(int x_is_f32) { return (x_is_f32 == 0 || x_is_f32 == 1) ? MMF_OK : MMF_ERR_DTYPE; }
 
-hipError_t run_fused_decode(const void* x, bool x_is_f32, const float* gamma,
-                            const uint32_t* Wpacked, const float* w_scale, float* y, int64_t M,
-                            int64_t K, int64_t N, hipStream_t stream) {
-  const size_t xsz = x_is_f32 ? 4 : 2;
-  for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
-    const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
-    mmf::DecodeArgs d{static_cast<const char*>(x) + m0 * K * xsz, x_is_f32, gamma, nullptr,
-                      nullptr, nullptr, Wpacked, w_scale, y + m0 * N, mt,
-                      static_cast<int>(K), N, mmf::Epilogue::kDequantF32};
-    const hipError_t e = mmf::launch_decode(d, stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
-}
-
 // Checks of the forward's arguments shared by the allocating and _ws forms.
-int check_fwd(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
+int check_fwd(int path, const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
               const float* w_scale, const float* y, int64_t M, int64_t K, int64_t N,
               bool gemm_only = false) {
   if (int st = check_shape(M, K, N)) return st;
   if (M == 0 || N == 0) return MMF_OK;
-  if (int st = check_from_x(M, K, N, x_is_f32, gemm_only)) return st;
+  if (int st = check_from_x(path, M, K, N, x_is_f32, gemm_only)) return st;
   if (!x || !Wpacked || !w_scale || !y) return MMF_ERR_NULL;
   if (!aligned16(x) || !aligned16(Wpacked) || !aligned16(y) || (gamma && !aligned16(gamma)))
     return MMF_ERR_ALIGN;
   return MMF_OK;
-}
-
-// `scratch` may be nullptr when fwd_need is 0.
-int run_fwd(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
-            const float* w_scale, float* y, int64_t M, int64_t K, int64_t N, char* scratch,
-            hipStream_t stream) {
-  const mmf::Epilogue ep = mmf::Epilogue::kDequantF32;
-  if (fused_decode(M, K, N, x_is_f32) && (scratch == nullptr || !prefers_skinny(M, K, N, x_is_f32, ep)))
-    return hip_status(run_fused_decode(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, stream));
-  return hip_status(quant_contract(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, ep, {}, scratch, stream, contract));
 }
 
 // Runs `run(scratch)` on the caller's workspace (checked against `need`), or
@@ -241,15 +229,28 @@ int with_workspace(void* workspace, size_t workspace_bytes, size_t need, hipStre
   return hip_status(fe);
 }
 
+// A forward from x without caller scratch: allocated stream-ordered here,
+// except for fused decode launches.
+int run_from_x_alloc(int path, const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
+                     const float* w_scales, float* out, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep,
+                     const mmf::Affine& aff, hipStream_t stream) {
+  Route route = route_from_x(path, M, K, N, x_is_f32, ep, true);
+  if (route != Route::kFusedDecode && fused_decode(path, M, K, N, x_is_f32) && capturing(stream))
+    route = Route::kFusedDecode;
+  const size_t need = route == Route::kFusedDecode ? 0 : fwd_scratch(M, K).total;
+  return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
+    return run_from_x(path, route, x, x_is_f32, gamma, Wpacked, w_scales, out, M, K, N, ep, aff, scratch, stream);
+  });
+}
+
 int fwd_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
               const float* w_scale, float* y, int64_t M, int64_t K, int64_t N,
               hipStream_t stream) {
-  if (int st = check_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
+  const int path = current_path();
+  if (int st = check_fwd(path, x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
   if (M == 0 || N == 0) return MMF_OK;
-  const size_t need = fwd_need(M, K, N, x_is_f32, mmf::Epilogue::kDequantF32, stream);
-  return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
-    return run_fwd(x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, scratch, stream);
-  });
+  return run_from_x_alloc(path, x, x_is_f32, gamma, Wpacked, w_scale, y, M, K, N, mmf::Epilogue::kDequantF32, {},
+                          stream);
 }
 
 int act_quant_common(const void* x, int x_is_f32, const float* gamma, int8_t* q,
@@ -266,74 +267,27 @@ int act_quant_common(const void* x, int x_is_f32, const float* gamma, int8_t* q,
                                           static_cast<int>(K), stream));
 }
 
-// GLU (gated up-projection): x -> RMSNorm + quantisation -> the interleaved
-// gate/up contraction with the SiLU(g) * u epilogue: fused decode launches for
-// the token counts the decode kernel takes, the MFMA kernel otherwise.
-int check_glu(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
+// GLU (gated up-projection): the interleaved gate/up contraction with the
+// SiLU(g) * u epilogue.
+int check_glu(int path, const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
               const float* w_scales, const float* p, int64_t M, int64_t K, int64_t L) {
   if (L < 0 || L > kMaxMN / 2 || (L % 16) != 0) return MMF_ERR_SHAPE;
   if (int st = check_shape(M, K, 2 * L)) return st;
   if (M == 0 || L == 0) return MMF_OK;
-  if (int st = check_from_x(M, K, 2 * L, x_is_f32, true)) return st;
+  if (int st = check_from_x(path, M, K, 2 * L, x_is_f32, true)) return st;
   if (!x || !Wgu || !w_scales || !p) return MMF_ERR_NULL;
   if (!aligned16(x) || !aligned16(Wgu) || !aligned16(p) || (gamma && !aligned16(gamma)))
     return MMF_ERR_ALIGN;
   return MMF_OK;
 }
 
-int run_glu(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
-            const float* w_scales, float* p, int64_t M, int64_t K, int64_t L, char* scratch,
-            hipStream_t stream) {
-  const mmf::Epilogue ep = mmf::Epilogue::kGluF32;
-  // few tokens: fused decode launches with the GLU epilogue (no scratch)
-  if (fused_decode(M, K, 2 * L, x_is_f32) &&
-      (scratch == nullptr || !prefers_skinny(M, K, 2 * L, x_is_f32, ep))) {
-    const size_t xsz = x_is_f32 ? 4 : 2;
-    for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
-      const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
-      mmf::DecodeArgs d{static_cast<const char*>(x) + m0 * K * xsz, x_is_f32, gamma, nullptr,
-                        nullptr, nullptr, Wgu, w_scales, p + m0 * L, mt,
-                        static_cast<int>(K), 2 * L, mmf::Epilogue::kGluF32};
-      if (mmf::launch_decode(d, stream) != hipSuccess) return MMF_ERR_HIP;
-    }
-    return MMF_OK;
-  }
-  return hip_status(quant_contract(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, 2 * L, ep, {}, scratch, stream,
-                                   contract_mfma));
-}
-
 int glu_alloc(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wgu,
               const float* w_scales, float* p, int64_t M, int64_t K, int64_t L,
               hipStream_t stream) {
-  if (int st = check_glu(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, L)) return st;
+  const int path = current_path();
+  if (int st = check_glu(path, x, x_is_f32, gamma, Wgu, w_scales, p, M, K, L)) return st;
   if (M == 0 || L == 0) return MMF_OK;
-  const size_t need = fwd_need(M, K, 2 * L, x_is_f32, mmf::Epilogue::kGluF32, stream);
-  return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
-    return run_glu(x, x_is_f32, gamma, Wgu, w_scales, p, M, K, L, scratch, stream);
-  });
-}
-
-// ---- affine forward (bias and per-segment activations after the dequant) ----
-
-// Fused decode launches for the token counts the fused kernel takes, else
-// activation quantisation into `scratch` (fwd_scratch) and the MFMA kernels.
-int run_affine(const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
-               const float* w_scales, const mmf::Affine& aff, float* y, int64_t M, int64_t K,
-               int64_t N, char* scratch, hipStream_t stream) {
-  const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
-  if (fused_decode(M, K, N, x_is_f32) && (scratch == nullptr || !prefers_skinny(M, K, N, x_is_f32, ep))) {
-    const size_t xsz = x_is_f32 ? 4 : 2;
-    for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
-      const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
-      mmf::DecodeArgs d{static_cast<const char*>(x) + m0 * K * xsz, x_is_f32, gamma, nullptr,
-                        nullptr, nullptr, Wpacked, w_scales, y + m0 * N, mt,
-                        static_cast<int>(K), N, ep, aff};
-      if (mmf::launch_decode(d, stream) != hipSuccess) return MMF_ERR_HIP;
-    }
-    return MMF_OK;
-  }
-  return hip_status(quant_contract(x, x_is_f32, gamma, Wpacked, w_scales, y, M, K, N, ep, aff, scratch, stream,
-                                   contract_mfma));
+  return run_from_x_alloc(path, x, x_is_f32, gamma, Wgu, w_scales, p, M, K, 2 * L, mmf::Epilogue::kGluF32, {}, stream);
 }
 
 bool aligned16_or_null(const void* p) { return p == nullptr || aligned16(p); }
@@ -571,14 +525,17 @@ int mmf_bitlinear_fwd_ws(const void* x, int x_is_f32, const float* gamma,
                          int64_t K, int64_t N, void* workspace, size_t workspace_bytes,
                          hipStream_t stream) {
   if (int st = check_dtype(x_is_f32)) return st;
-  if (int st = check_fwd(x, x_is_f32 == 1, gamma, Wpacked, w_scale, y, M, K, N)) return st;
+  const int path = current_path();
+  const bool f32 = x_is_f32 == 1;
+  if (int st = check_fwd(path, x, f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
   if (M == 0 || N == 0) return MMF_OK;
   if (!workspace) return MMF_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(workspace) & (kScratchAlign - 1)) != 0 ||
       workspace_bytes < fwd_scratch(M, K).total)
     return MMF_ERR_WORKSPACE;
-  return run_fwd(x, x_is_f32 == 1, gamma, Wpacked, w_scale, y, M, K, N,
-                 static_cast<char*>(workspace), stream);
+  const mmf::Epilogue ep = mmf::Epilogue::kDequantF32;
+  return run_from_x(path, route_from_x(path, M, K, N, f32, ep, true), x, f32, gamma, Wpacked, w_scale, y, M, K, N, ep,
+                    {}, static_cast<char*>(workspace), stream);
 }
 
 size_t mmf_bitlinear_noalloc_max_bytes(void) { return kNoAllocScratchBytes; }
@@ -587,39 +544,45 @@ int mmf_bitlinear_fwd_noalloc(const void* x, int x_is_f32, const float* gamma,
                               const uint32_t* Wpacked, const float* w_scale, float* y, int64_t M,
                               int64_t K, int64_t N, hipStream_t stream) {
   if (int st = check_dtype(x_is_f32)) return st;
-  if (int st = check_fwd(x, x_is_f32 == 1, gamma, Wpacked, w_scale, y, M, K, N)) return st;
-  if (M == 0 || N == 0) return MMF_OK;
+  const int path = current_path();
   const bool f32 = x_is_f32 == 1;
+  if (int st = check_fwd(path, x, f32, gamma, Wpacked, w_scale, y, M, K, N)) return st;
+  if (M == 0 || N == 0) return MMF_OK;
+  const mmf::Epilogue ep = mmf::Epilogue::kDequantF32;
   // few tokens: fused decode launches, which use no scratch
-  if (fused_decode(M, K, N, f32))
-    return hip_status(run_fused_decode(x, f32, gamma, Wpacked, w_scale, y, M, K, N, stream));
-  if (fwd_scratch(M, K).total > kNoAllocScratchBytes) return MMF_ERR_WORKSPACE;
-  int st = MMF_OK;
-  char* ws = device_scratch(&st);
-  if (ws == nullptr) return st;
-  return run_fwd(x, f32, gamma, Wpacked, w_scale, y, M, K, N, ws, stream);
+  const Route route = route_from_x(path, M, K, N, f32, ep, false);
+  char* ws = nullptr;
+  if (route != Route::kFusedDecode) {
+    if (fwd_scratch(M, K).total > kNoAllocScratchBytes) return MMF_ERR_WORKSPACE;
+    int st = MMF_OK;
+    ws = device_scratch(&st);
+    if (ws == nullptr) return st;
+  }
+  return run_from_x(path, route, x, f32, gamma, Wpacked, w_scale, y, M, K, N, ep, {}, ws, stream);
 }
 
 int mmf_ternary_gemm_dequant(const int8_t* q, const float* a_scale, const int32_t* q_rowsum,
                              const uint32_t* Wpacked, const float* w_scale, float* y, int64_t M,
                              int64_t K, int64_t N, hipStream_t stream) {
+  const int path = current_path();
   if (int st = check_shape(M, K, N)) return st;
   if (M == 0 || N == 0) return MMF_OK;
-  if (int st = check_contract(M, K, N)) return st;
+  if (int st = check_contract(path, M, K, N)) return st;
   if (!q || !a_scale || !q_rowsum || !Wpacked || !w_scale || !y) return MMF_ERR_NULL;
   if (!aligned16(q) || !aligned16(a_scale) || !aligned16(q_rowsum) || !aligned16(Wpacked) ||
       !aligned16(y))
     return MMF_ERR_ALIGN;
   mmf::ContractArgs a{q, a_scale, q_rowsum, Wpacked, w_scale, y, M, static_cast<int>(K), N,
                       mmf::Epilogue::kDequantF32};
-  return hip_status(contract(a, stream));
+  return hip_status(contract(path, a, stream));
 }
 
 int mmf_ternary_gemm_i32(const int8_t* q, const uint32_t* Wpacked, int32_t* acc, int64_t M,
                          int64_t K, int64_t N, hipStream_t stream) {
+  const int path = current_path();
   if (int st = check_shape(M, K, N)) return st;
   if (M == 0 || N == 0) return MMF_OK;
-  if (int st = check_contract(M, K, N)) return st;
+  if (int st = check_contract(path, M, K, N)) return st;
   if (!q || !Wpacked || !acc) return MMF_ERR_NULL;
   if (!aligned16(q) || !aligned16(Wpacked) || !aligned16(acc)) return MMF_ERR_ALIGN;
   void* rowsum = nullptr;
@@ -631,7 +594,7 @@ int mmf_ternary_gemm_i32(const int8_t* q, const uint32_t* Wpacked, int32_t* acc,
   if (e == hipSuccess) {
     mmf::ContractArgs a{q, nullptr, rs, Wpacked, nullptr, acc, M, static_cast<int>(K), N,
                         mmf::Epilogue::kRawI32};
-    e = contract(a, stream);
+    e = contract(path, a, stream);
   }
   const hipError_t fe = hipFreeAsync(rowsum, stream);
   if (e != hipSuccess) return MMF_ERR_HIP;
@@ -664,14 +627,17 @@ int mmf_glu_fwd_ws(const void* x, int x_is_f32, const float* gamma, const uint32
                    const float* w_scales, float* p, int64_t M, int64_t K, int64_t L,
                    void* workspace, size_t workspace_bytes, hipStream_t stream) {
   if (int st = check_dtype(x_is_f32)) return st;
-  if (int st = check_glu(x, x_is_f32 == 1, gamma, Wgu_packed, w_scales, p, M, K, L)) return st;
+  const int path = current_path();
+  const bool f32 = x_is_f32 == 1;
+  if (int st = check_glu(path, x, f32, gamma, Wgu_packed, w_scales, p, M, K, L)) return st;
   if (M == 0 || L == 0) return MMF_OK;
   if (!workspace) return MMF_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(workspace) & (kScratchAlign - 1)) != 0 ||
       workspace_bytes < fwd_scratch(M, K).total)
     return MMF_ERR_WORKSPACE;
-  return run_glu(x, x_is_f32 == 1, gamma, Wgu_packed, w_scales, p, M, K, L,
-                 static_cast<char*>(workspace), stream);
+  const mmf::Epilogue ep = mmf::Epilogue::kGluF32;
+  return run_from_x(path, route_from_x(path, M, K, 2 * L, f32, ep, true), x, f32, gamma, Wgu_packed, w_scales, p, M, K,
+                    2 * L, ep, {}, static_cast<char*>(workspace), stream);
 }
 
 int mmf_ternary_gemm_glu(const int8_t* q, const float* a_scale, const int32_t* q_rowsum,
@@ -687,14 +653,16 @@ int mmf_ternary_gemm_glu(const int8_t* q, const float* a_scale, const int32_t* q
     return MMF_ERR_ALIGN;
   mmf::ContractArgs a{q, a_scale, q_rowsum, Wgu_packed, w_scales, p, M, static_cast<int>(K), 2 * L,
                       mmf::Epilogue::kGluF32};
-  return hip_status(contract_mfma(a, stream));
+  return hip_status(contract_mfma(current_path(), a, stream));
 }
 
 int mmf_bitlinear_fwd_bias(const void* x, int x_is_f32, const float* gamma,
                            const uint32_t* Wpacked, const float* w_scale, const float* bias,
                            float* y, int64_t M, int64_t K, int64_t N, hipStream_t stream) {
   if (int st = check_dtype(x_is_f32)) return st;
-  if (int st = check_fwd(x, x_is_f32 == 1, gamma, Wpacked, w_scale, y, M, K, N, true)) return st;
+  const int path = current_path();
+  const bool f32 = x_is_f32 == 1;
+  if (int st = check_fwd(path, x, f32, gamma, Wpacked, w_scale, y, M, K, N, true)) return st;
   if (N % 4 != 0) return MMF_ERR_SHAPE;
   if (M == 0 || N == 0) return MMF_OK;
   if (!bias) return MMF_ERR_NULL;
@@ -703,10 +671,7 @@ int mmf_bitlinear_fwd_bias(const void* x, int x_is_f32, const float* gamma,
   aff.bias = bias;
   aff.seg = N;
   aff.acts = mmf::kActIdentity;
-  const size_t need = fwd_need(M, K, N, x_is_f32 == 1, mmf::Epilogue::kAffineF32, stream);
-  return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
-    return run_affine(x, x_is_f32 == 1, gamma, Wpacked, w_scale, aff, y, M, K, N, scratch, stream);
-  });
+  return run_from_x_alloc(path, x, f32, gamma, Wpacked, w_scale, y, M, K, N, mmf::Epilogue::kAffineF32, aff, stream);
 }
 
 size_t mmf_mlgru_proj_workspace_bytes(int64_t M, int64_t K, int64_t d) {
@@ -721,14 +686,18 @@ int mmf_mlgru_proj(const void* x, int x_is_f32, const float* gamma, const uint32
   if (int st = check_dtype(x_is_f32)) return st;
   if (int st = check_mlgru_proj(x, gamma, Wfcg, w_scales, bias, lb, fcg, M, K, d)) return st;
   if (M == 0) return MMF_OK;
-  if (int st = check_from_x(M, K, 3 * d, x_is_f32 == 1, true)) return st;
+  const int path = current_path();
+  const bool f32 = x_is_f32 == 1;
+  if (int st = check_from_x(path, M, K, 3 * d, f32, true)) return st;
   mmf::Affine aff;
   aff.bias = bias;
   aff.lb = lb;
   aff.seg = d;
   aff.acts = kMlgruActs;
   return with_workspace(workspace, workspace_bytes, fwd_scratch(M, K).total, stream, [&](char* scratch) {
-    return run_affine(x, x_is_f32 == 1, gamma, Wfcg, w_scales, aff, fcg, M, K, 3 * d, scratch, stream);
+    const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
+    return run_from_x(path, route_from_x(path, M, K, 3 * d, f32, ep, true), x, f32, gamma, Wfcg, w_scales, fcg, M, K,
+                      3 * d, ep, aff, scratch, stream);
   });
 }
 
@@ -751,7 +720,7 @@ int mmf_mlgru_proj_q(const int8_t* q, const float* a_scale, const int32_t* q_row
   aff.acts = kMlgruActs;
   mmf::ContractArgs a{q, a_scale, q_rowsum, Wfcg, w_scales, fcg, M, static_cast<int>(K), 3 * d,
                       mmf::Epilogue::kAffineF32, aff};
-  return hip_status(contract_mfma(a, stream));
+  return hip_status(contract_mfma(current_path(), a, stream));
 }
 
 size_t mmf_mlgru_scan_workspace_bytes(int64_t B, int64_t T, int64_t d) {
@@ -785,8 +754,10 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
   if (B < 0 || T < 0 || B > kMaxMN || T > kMaxMN || (T > 0 && B > kMaxMN / T)) return MMF_ERR_SHAPE;
   const int64_t M = B * T;
   if (M == 0) return MMF_OK;
-  if (int st = check_from_x(M, d, 3 * d, x_is_f32 == 1, true)) return st;
-  if (int st = check_from_x(M, d, d, true, true)) return st;
+  const int path = current_path();
+  const bool f32 = x_is_f32 == 1;
+  if (int st = check_from_x(path, M, d, 3 * d, f32, true)) return st;
+  if (int st = check_from_x(path, M, d, d, true, true)) return st;
   if (!x || !Wfcg || !w_scales || !Wo || !w_scale_o || !o) return MMF_ERR_NULL;
   if (!aligned16(x) || !aligned16(Wfcg) || !aligned16(Wo) || !aligned16(o) ||
       !aligned16_or_null(gamma) || !aligned16_or_null(bias) || !aligned16_or_null(lb) ||
@@ -802,8 +773,9 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
     in.lb = lb;
     in.seg = d;
     in.acts = kMlgruActs;
-    int st = run_affine(x, x_is_f32 == 1, gamma, Wfcg, w_scales, in, fcg, M, d, 3 * d,
-                        scratch + s.q_off, stream);
+    const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
+    int st = run_from_x(path, route_from_x(path, M, d, 3 * d, f32, ep, true), x, f32, gamma, Wfcg, w_scales, fcg, M, d,
+                        3 * d, ep, in, scratch + s.q_off, stream);
     if (st != MMF_OK) return st;
     mmf::Affine out;
     out.bias = b_o;
@@ -813,13 +785,12 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
     // array: the recurrence and output gate run in the output projection's
     // prologue (no launch, no o' round trip).  Identical arithmetic to the
     // separate kernels, so identical results.
-    const bool fused_decode_out =
-        fused_decode(M, d, d, true) && !prefers_skinny(M, d, d, true, mmf::Epilogue::kAffineF32);
-    if (T == 1 && (h_last == nullptr || h_last != h0) && fused_decode_out) {
+    const Route route = route_from_x(path, M, d, d, true, ep, true);
+    if (T == 1 && (h_last == nullptr || h_last != h0) && route == Route::kFusedDecode) {
       for (int64_t m0 = 0; m0 < M; m0 += kDecodeMaxTokens) {
         const int64_t mt = M - m0 < kDecodeMaxTokens ? M - m0 : kDecodeMaxTokens;
         mmf::DecodeArgs a{fcg + m0 * 3 * d, true, gamma_o, nullptr, nullptr, nullptr, Wo, w_scale_o,
-                          o + m0 * d, mt, static_cast<int>(d), d, mmf::Epilogue::kAffineF32, out};
+                          o + m0 * d, mt, static_cast<int>(d), d, ep, out};
         a.mlgru_in = true;
         a.h_in = h0 ? h0 + m0 * d : nullptr;
         a.h_out = h_last ? h_last + m0 * d : nullptr;
@@ -830,24 +801,23 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
     // More sequences, or the state updated in place: the step and the output
     // gate in the activation quantisation, whose rows each belong to one
     // workgroup (no o' round trip, one launch less; the same bits).
-    if (T == 1 && !fused_decode_out && mmf::act_quant_mlgru_fits(static_cast<int>(d))) {
+    if (T == 1 && route != Route::kFusedDecode && mmf::act_quant_mlgru_fits(static_cast<int>(d))) {
       const FwdScratch f = fwd_scratch(M, d);
       char* const qs = scratch + s.q_off;
       int8_t* q = reinterpret_cast<int8_t*>(qs + f.q_off);
       float* a_scale = reinterpret_cast<float*>(qs + f.a_off);
       int32_t* rowsum = reinterpret_cast<int32_t*>(qs + f.r_off);
-      const mmf::Epilogue ep = mmf::Epilogue::kAffineF32;
-      const bool tiled = use_skinny(M, d, d, ep, true);
+      const bool tiled = route == Route::kTiledQ;
       if (mmf::launch_act_quant_mlgru(fcg, h0, h_last, gamma_o, q, a_scale, rowsum, M, static_cast<int>(d), stream,
                                       tiled) != hipSuccess)
         return MMF_ERR_HIP;
       const mmf::ContractArgs a{q, a_scale, rowsum, Wo, w_scale_o, o, M, static_cast<int>(d), d, ep, out};
-      return hip_status(tiled ? mmf::launch_skinny(a, true, stream) : contract_mfma(a, stream));
+      return hip_status(tiled ? mmf::launch_skinny(a, true, stream) : contract_mfma(path, a, stream));
     }
     if (mmf::launch_mlgru_scan(fcg, h0, op, h_last, B, T, d, reinterpret_cast<float*>(scratch + s.scan_off),
                                stream) != hipSuccess)
       return MMF_ERR_HIP;
-    return run_affine(op, true, gamma_o, Wo, w_scale_o, out, o, M, d, d, scratch + s.q_off, stream);
+    return run_from_x(path, route, op, true, gamma_o, Wo, w_scale_o, o, M, d, d, ep, out, scratch + s.q_off, stream);
   });
 }
 
@@ -883,7 +853,7 @@ int mmf_bitlinear_train_fwd(const void* x, int x_is_f32, const float* gamma, con
     aff.acts = mmf::kActIdentity;
     mmf::ContractArgs a{q, a_scale, rowsum, Wpacked, w_scale, y, M, static_cast<int>(K), N,
                         bias ? mmf::Epilogue::kAffineF32 : mmf::Epilogue::kDequantF32, aff};
-    return hip_status(contract_mfma(a, stream));
+    return hip_status(contract_mfma(current_path(), a, stream));
   });
 }
 

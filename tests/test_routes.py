@@ -17,3 +17,34 @@ def test_backward_of_very_many_tokens_launches():
     inside the runtime's limit of 2^32 threads."""
     for r in record([bwd((1 << 24) + 7, 16, 3), bwd(1 << 25, 16, 60)]):
         assert r["status"] == 0 and kernels(r)[0] == "pad_rows_kernel"
+
+
+# Calls whose form depends on the process-wide path: M of 8 and 20 rows fit the
+# fused decode kernel, 45 and 300 do not (K = 2048), with and without scratch.
+def _path_calls(M, **kw):
+    K, N, d = 2048, 6144, 2048
+    return [call("mmf_bitlinear_fwd", A, A, A, A, A, M, K, N, None, **kw),
+            call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, M, K, N, A, BIG, None, **kw),
+            call("mmf_bitlinear_fwd_noalloc", A, 0, A, A, A, A, M, K, N, None, **kw),
+            call("mmf_bitlinear_fwd_bias", A, 0, A, A, A, A, A, M, K, N, None, **kw),
+            call("mmf_glu_fwd", A, A, A, A, A, M, K, N // 2, None, **kw),
+            call("mmf_mlgru_fwd", A, 0, A, A, A, A, A, A, A, A, A, A, A, A, M, 1, d, None, 0, None, **kw),
+            call("mmf_ternary_gemm_dequant", A, A, A, A, A, A, M, K, N, None, **kw)]
+
+
+@pytest.mark.parametrize("capture", [False, True])
+@pytest.mark.parametrize("path,other", [(AUTO, GEMM), (AUTO, GEMV), (GEMV, AUTO), (GEMM, GEMV)])
+def test_a_path_set_meanwhile_does_not_reach_a_running_call(path, other, capture):
+    """Another thread's mmf_set_path during a call leaves that call as it was:
+    the same kernels, and scratch wherever act-quant writes."""
+    Ms, ns = (8, 20, 45, 300), range(1, 6)
+    out = record([c for M in Ms for n in (0, *ns) for c in _path_calls(M, path=path, capture=capture, switch=(n, other))])
+    per = len(_path_calls(1))
+    for i in range(len(Ms)):
+        runs = [out[(i * (len(ns) + 1) + n) * per:][:per] for n in (0, *ns)]
+        for got in runs:  # the first one is undisturbed
+            for w, g in zip(runs[0], got):
+                assert w["launches"]
+                assert [(x["kernel"], x["grid"]) for x in g["launches"]] == [(x["kernel"], x["grid"]) for x in w["launches"]]
+                assert (g["status"], g["allocs"], g["frees"]) == (0, w["allocs"], w["allocs"])
+                assert all(x["args"][2] >= A for x in g["launches"] if x["kernel"].startswith("act_quant_kernel"))
