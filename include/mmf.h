@@ -137,9 +137,10 @@ int mmf_act_quant_ex(const void *x, int x_is_f32, const float *gamma, int8_t *q,
  * MFMA over 16 columns by the token rows), a few hundred act-quant and the
  * int8 MFMA kernel that splits K over the waves of a workgroup, larger M
  * act-quant and the tiled int8 MFMA GEMM kernel; all give the same bits.
- * Allocates its M*K + 8*M byte scratch stream-ordered (hipMallocAsync) beyond
- * the fused decode kernel; under stream capture, up to 32 tokens (K <= 2048)
- * or 64 (larger K) run as decode launches of 16 tokens, which need none.
+ * Allocates its M*K + 8*M byte scratch stream-ordered (hipMallocAsync), except
+ * where the fused decode kernel takes 16 token rows of this K (up to 2048 in
+ * bf16, 1024 in float32): up to 32 tokens then run as launches of 16 tokens,
+ * which need none.
  * mmf_bitlinear_fwd_ws takes caller scratch instead.
  * x: [M][K] bf16 bits; gamma: [K] or NULL; Wpacked: [K/16][N]; w_scale: [1];
  * y: [M][N] float32 out.
@@ -170,15 +171,15 @@ int mmf_bitlinear_fwd_ws(const void *x, int x_is_f32, const float *gamma,
 /*
  * mmf_bitlinear_fwd for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the same kernels and results as mmf_bitlinear_fwd_ws, with the
+ * hipMalloc): the results of mmf_bitlinear_fwd_ws bit for bit, with the
  * scratch (q, a_scale, q_rowsum: mmf_bitlinear_workspace_bytes(M, K) bytes)
  * in a static device array of mmf_bitlinear_noalloc_max_bytes() = 64 MiB
  * that each GPU the library runs on holds until the process ends.  No call
  * allocates or frees memory; the array's address is looked up once per
  * device, on the first call there.  Calls that need more scratch than the
- * array holds return MMF_ERR_WORKSPACE before anything is enqueued (the
- * fused decode kernel, up to 32 tokens at K <= 2048 and 64 beyond, needs
- * none).  Every call on a GPU shares that
+ * array holds return MMF_ERR_WORKSPACE before anything is enqueued; calls
+ * that run as fused decode launches (see mmf_bitlinear_fwd) need none.
+ * Every call on a GPU shares that
  * GPU's array: calls that overlap on one GPU (on different streams, or from
  * different host threads) race; serialise them.  The array keeps the last
  * call's contents, which every call overwrites before reading.

@@ -50,10 +50,11 @@ int current_path() { return g_path.load(std::memory_order_relaxed); }
 
 // Whether rows run as decode launches of at most 16 tokens each: on the
 // automatic path up to decode_max_tokens(K) tokens, when the decode kernel
-// takes such a slice (its LDS holds q of 16 tokens up to K = 7680).  Beyond 16
-// tokens that is the form without scratch (route_from_x takes the K-split
-// kernel where there is some); it was set against the tiled MFMA kernel, whose
-// time at a small M is one tile's k loop (forward calls from x, slices at 16 /
+// takes such a slice (from x: 16 rows in the registers of its waves, bf16 up
+// to K = 2048; from rows of q: in its LDS, up to K = 7680).  Beyond 16 tokens
+// that is the form without scratch, and what remains where the K-split kernel
+// refuses (2 GiB of weights); the limits were set against the tiled MFMA
+// kernel, whose time at a small M is one tile's k loop (forward calls at 16 /
 // 32 / 48 / 64 tokens against the tiled kernel at 16-128 tokens: K = 2048, N =
 // 6144: 6.7 / 12.7 / 18.6 / 24.5 us against 15.2-17.2; K = 5120, N = 15360:
 // 11.5 / 16.7 / 21.6 / 26.8 against 35.2-37.3).  MMF_PATH_GEMV forces the
@@ -131,22 +132,14 @@ bool fused_decode(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32) {
 // q for the others.  More than 16 tokens prefer the K-split kernel where there
 // is scratch: the fused kernel's row stage repeats in every workgroup and each
 // further 16 tokens stream the weights again (forward calls from bf16 x,
-// slices -> act-quant + K-split, us: 17 x 1024 x 6144 8.0 -> 5.9,
-// 32 x 2048 x 6144 12.9 -> 6.4, 64 x 5120 x 27648 49.0 -> 20.4).
+// slices -> act-quant + K-split, us: 17 x 512 x 1024 6.6 -> 4.7,
+// 17 x 1024 x 6144 8.0 -> 5.9, 32 x 2048 x 6144 12.9 -> 6.5).
 enum class Route { kFusedDecode, kTiledQ, kRows };
 Route route_from_x(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep, bool scratch) {
   const bool fused = fused_decode(path, M, K, N, x_is_f32);
   if (fused && (M <= kDecodeMaxTokens || !scratch)) return Route::kFusedDecode;
   if (!one_decode_launch(M, K, N, ep) && use_skinny(path, M, K, N, ep, true)) return Route::kTiledQ;
   return fused ? Route::kFusedDecode : Route::kRows;
-}
-
-// Whether work on `stream` is being captured into a graph (or that cannot be
-// told): calls that would only now need scratch then keep the fused decode
-// launches, which allocate nothing.
-bool capturing(hipStream_t stream) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
 }
 
 // A forward from x on `route` (scratch: fwd_scratch(M, K), not used by fused
@@ -229,14 +222,17 @@ int with_workspace(void* workspace, size_t workspace_bytes, size_t need, hipStre
   return hip_status(fe);
 }
 
-// A forward from x without caller scratch: allocated stream-ordered here,
-// except for fused decode launches.
+// A forward from x without caller scratch: as fused decode launches where those
+// take it (up to 32 tokens), else with scratch allocated stream-ordered here.
+// Allocating and freeing costs more than the launch and the kernel time that
+// the K-split kernel saves (forward calls back to back, us, two decode
+// launches / allocated: 17 x 256 x 256 8.4 / 21.9, 20 x 2048 x 6144 11.3 /
+// 23.9, 32 x 2048 x 2048 12.1 / 22.1, 32 x 2048 x 11264 13.9 / 24.2), and a
+// call that needs no memory also runs where there is none, or under capture.
 int run_from_x_alloc(int path, const void* x, bool x_is_f32, const float* gamma, const uint32_t* Wpacked,
                      const float* w_scales, float* out, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep,
                      const mmf::Affine& aff, hipStream_t stream) {
-  Route route = route_from_x(path, M, K, N, x_is_f32, ep, true);
-  if (route != Route::kFusedDecode && fused_decode(path, M, K, N, x_is_f32) && capturing(stream))
-    route = Route::kFusedDecode;
+  const Route route = route_from_x(path, M, K, N, x_is_f32, ep, false);
   const size_t need = route == Route::kFusedDecode ? 0 : fwd_scratch(M, K).total;
   return with_workspace(nullptr, 0, need, stream, [&](char* scratch) {
     return run_from_x(path, route, x, x_is_f32, gamma, Wpacked, w_scales, out, M, K, N, ep, aff, scratch, stream);

@@ -48,3 +48,31 @@ def test_a_path_set_meanwhile_does_not_reach_a_running_call(path, other, capture
                 assert [(x["kernel"], x["grid"]) for x in g["launches"]] == [(x["kernel"], x["grid"]) for x in w["launches"]]
                 assert (g["status"], g["allocs"], g["frees"]) == (0, w["allocs"], w["allocs"])
                 assert all(x["args"][2] >= A for x in g["launches"] if x["kernel"].startswith("act_quant_kernel"))
+
+
+def _alloc_calls(M, K, **kw):
+    N = 1024
+    # the fused kernel takes 16 rows up to K = 2048 in bf16, 1024 in float32
+    f32 = [call("mmf_bitlinear_fwd_f32", A, A, A, A, A, M, K, N, None, **kw)] if K <= 1024 else []
+    return f32 + [call("mmf_bitlinear_fwd", A, A, A, A, A, M, K, N, None, **kw),
+                  call("mmf_bitlinear_fwd_noalloc", A, 0, A, A, A, A, M, K, N, None, **kw),
+                  call("mmf_bitlinear_fwd_bias", A, 0, A, A, A, A, A, M, K, N, None, **kw),
+                  call("mmf_glu_fwd", A, A, A, A, A, M, K, N // 2, None, **kw)]
+
+
+@pytest.mark.parametrize("M,K", [(1, 2048), (16, 2048), (17, 16), (20, 2048), (32, 1024), (32, 2048)])
+def test_few_tokens_without_workspace_allocate_nothing(M, K):
+    """Forms without caller scratch run up to 32 tokens as fused decode
+    launches: no allocation, which would cost more than the second launch, can
+    fail, and cannot be captured everywhere."""
+    for r in record([c for kw in ({}, {"fail_alloc": True}, {"capture": True}) for c in _alloc_calls(M, K, **kw)]):
+        assert (r["status"], r["allocs"]) == (0, 0)
+        assert kernels(r) == ["decode_kernel"] * -(-M // 16)
+
+
+def test_calls_that_need_scratch_allocate_it():
+    for M, K in ((17, 2064), (33, 2048), (65, 4096)):
+        for r in record(_alloc_calls(M, K)):
+            assert r["status"] == 0 and r["allocs"] == r["frees"] and kernels(r) == ["act_quant_kernel", "skinny_kernel"]
+        failed = [r["status"] for r in record(_alloc_calls(M, K, fail_alloc=True))]
+        assert failed == [5, 0, 5, 5]  # the second form's scratch is static
