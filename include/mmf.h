@@ -133,14 +133,15 @@ int mmf_act_quant_ex(const void *x, int x_is_f32, const float *gamma, int8_t *q,
  *   y[m][n] = a_scale[m] * w_scale * sum_k q[m][k] t[n][k]
  * with q, a_scale from the act-quant step above and t from Wpacked.  The
  * integer sum is exact; the product is fp32 (a_scale[m] * w_scale first).
- * Up to 16 tokens take the fused decode kernel (one launch; 16x16x64 int8
- * MFMA over 16 columns by the token rows), a few hundred act-quant and the
- * int8 MFMA kernel that splits K over the waves of a workgroup, larger M
- * act-quant and the tiled int8 MFMA GEMM kernel; all give the same bits.
- * Allocates its M*K + 8*M byte scratch stream-ordered (hipMallocAsync), except
- * where the fused decode kernel takes 16 token rows of this K (up to 2048 in
- * bf16, 1024 in float32): up to 32 tokens then run as launches of 16 tokens,
- * which need none.
+ * Up to 16 tokens take the fused decode kernel where it holds them (one
+ * launch; 16x16x64 int8 MFMA over 16 columns by the token rows), more act-quant
+ * and an int8 MFMA kernel: the one that splits K over the waves of a workgroup
+ * where that is estimated faster (a few hundred rows into wide outputs, one to
+ * two thousand into outputs as narrow as K), else the tiled GEMM; all give the
+ * same bits.  Allocates its M*K + 8*M byte scratch stream-ordered
+ * (hipMallocAsync), except where the call runs as fused decode launches of at
+ * most 16 tokens, which need none: up to 32 tokens at K <= 2048 in bf16 or
+ * K <= 1024 in float32, fewer at larger K.
  * mmf_bitlinear_fwd_ws takes caller scratch instead.
  * x: [M][K] bf16 bits; gamma: [K] or NULL; Wpacked: [K/16][N]; w_scale: [1];
  * y: [M][N] float32 out.
@@ -402,11 +403,11 @@ int mmf_bitlinear_bwd(const uint16_t *dO, const void *x, int x_is_f32, const flo
                       void *workspace, size_t workspace_bytes, hipStream_t stream);
 
 /*
- * Kernel selection for the contraction: MMF_PATH_AUTO (the fused decode
- * kernel for M <= 16, the K-split kernel for a few hundred rows, the tiled
- * GEMM kernel otherwise; see mmf_bitlinear_fwd), MMF_PATH_GEMV or MMF_PATH_GEMM force one kernel for every M (the decode
+ * Kernel selection for the contraction: MMF_PATH_AUTO (the fused decode, the
+ * K-split or the tiled GEMM kernel by size; see mmf_bitlinear_fwd),
+ * MMF_PATH_GEMV or MMF_PATH_GEMM force one kernel for every M (the decode
  * kernel handles at most 16 tokens per launch and is launched once per
- * 16-token slice when forced).  Process-wide; returns
+ * 16-token slice when forced).  Process-wide, read once by each call; returns
  * the previous setting, or -MMF_ERR_ARG for an unknown value.
  */
 #define MMF_PATH_AUTO 0

@@ -662,13 +662,19 @@ int gemm_tile_choice(int64_t rows, int64_t N, int cus) {
 // (ragged stores), measured at 1937 x 2288 x 3998 45 -> 21 us.
 constexpr int64_t kRaggedMinRows = 257;
 
-double gemm_alone_us(int64_t rows, int K, int64_t N, int cus) {
+// Rounds of workgroups over the CUs x the time of one tile's k loop (longest
+// where the tile has the CU to itself), the packed weights through HBM, and
+// the launch; fitted to 2001 shapes (K = 512 to 13824, N = 64 to 27648, M = 17
+// to 16384; within 20 %).  What the K-split kernel shares (act-quant, the
+// outputs) is left out.
+double gemm_us(int64_t rows, int K, int64_t N, int cus) {
   struct Shape { int64_t bm, bn; double us, us_per_k; };
   constexpr Shape kShapes[] = {
-      {128, 512, 3.2, 0.0099}, {64, 512, 3.2, 0.0066}, {64, 256, 3.2, 0.0038}, {256, 256, 8.0, 0.0125}};
+      {128, 512, 0.4, 0.0075}, {64, 512, 0.1, 0.0050}, {64, 256, 0.0, 0.0037}, {256, 256, 11.0, 0.0087}};
   const Shape& s = kShapes[N % 4 != 0 && rows < kRaggedMinRows ? 3 : gemm_tile_choice(rows, N, cus)];
   const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), c = cus > 0 ? cus : 256;
-  return static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K);
+  return 2.3 + static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K) +
+         0.055e-6 * static_cast<double>(K) * static_cast<double>(N);
 }
 
 int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus) {

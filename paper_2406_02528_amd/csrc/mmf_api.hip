@@ -71,9 +71,14 @@ bool use_decode(int path, int64_t M, int64_t K, int64_t N, bool from_x, bool x_i
 }
 
 // Whether the automatic path contracts these rows with K split over the waves
-// of a workgroup (skinny.hip).
-bool use_skinny(int path, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep, bool tiled) {
-  return path == MMF_PATH_AUTO && mmf::skinny_takes(M, static_cast<int>(K), N, ep, tiled, mmf::device_cus());
+// of a workgroup (skinny.hip); `over_slices`: the alternative is decode
+// launches of 16 tokens, which measured slower at each of 820 shapes of 17 to
+// 64 rows (from x 32 x 7680 x 11264 20.8 -> 16.3 us, 26 x 32 x 58752 20.2 ->
+// 7.7), and not the tiled kernel.
+bool use_skinny(int path, int64_t M, int64_t K, int64_t N, mmf::Epilogue ep, bool tiled, bool over_slices) {
+  const int Ki = static_cast<int>(K);
+  return path == MMF_PATH_AUTO && mmf::skinny_fits(M, Ki, N, ep) &&
+         (over_slices || mmf::skinny_beats_gemm(M, Ki, N, ep, tiled, mmf::device_cus()));
 }
 
 // Whether the decode kernel contracts these rows of q in one launch (its
@@ -86,7 +91,7 @@ bool one_decode_launch(int64_t M, int64_t K, int64_t N, mmf::Epilogue ep) {
 // The MFMA contraction from rows of q: the K-split kernel for few rows, else
 // the tiled GEMM kernel.
 hipError_t contract_mfma(int path, const mmf::ContractArgs& a, hipStream_t stream) {
-  if (use_skinny(path, a.M, a.K, a.N, a.epilogue, false)) return mmf::launch_skinny(a, false, stream);
+  if (use_skinny(path, a.M, a.K, a.N, a.epilogue, false, false)) return mmf::launch_skinny(a, false, stream);
   return mmf::launch_gemm(a, stream);
 }
 
@@ -95,9 +100,11 @@ hipError_t contract_mfma(int path, const mmf::ContractArgs& a, hipStream_t strea
 // of 16 tokens runs as a decode launch, those whose q does not fit LDS reading
 // it from global memory.
 hipError_t contract(int path, const mmf::ContractArgs& a, hipStream_t stream) {
-  if (!one_decode_launch(a.M, a.K, a.N, a.epilogue) && use_skinny(path, a.M, a.K, a.N, a.epilogue, false))
+  const bool slices = use_decode(path, a.M, a.K, a.N, false, false);
+  if (!one_decode_launch(a.M, a.K, a.N, a.epilogue) &&
+      use_skinny(path, a.M, a.K, a.N, a.epilogue, false, slices))
     return mmf::launch_skinny(a, false, stream);
-  if (!use_decode(path, a.M, a.K, a.N, false, false)) return mmf::launch_gemm(a, stream);
+  if (!slices) return mmf::launch_gemm(a, stream);
   for (int64_t m0 = 0; m0 < a.M; m0 += kDecodeMaxTokens) {
     const int64_t mt = a.M - m0 < kDecodeMaxTokens ? a.M - m0 : kDecodeMaxTokens;
     const bool raw = a.epilogue == mmf::Epilogue::kRawI32;
@@ -138,7 +145,8 @@ enum class Route { kFusedDecode, kTiledQ, kRows };
 Route route_from_x(int path, int64_t M, int64_t K, int64_t N, bool x_is_f32, mmf::Epilogue ep, bool scratch) {
   const bool fused = fused_decode(path, M, K, N, x_is_f32);
   if (fused && (M <= kDecodeMaxTokens || !scratch)) return Route::kFusedDecode;
-  if (!one_decode_launch(M, K, N, ep) && use_skinny(path, M, K, N, ep, true)) return Route::kTiledQ;
+  const bool slices = fused || (ep == mmf::Epilogue::kDequantF32 && use_decode(path, M, K, N, false, false));
+  if (!one_decode_launch(M, K, N, ep) && use_skinny(path, M, K, N, ep, true, slices)) return Route::kTiledQ;
   return fused ? Route::kFusedDecode : Route::kRows;
 }
 

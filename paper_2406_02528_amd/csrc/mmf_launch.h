@@ -117,9 +117,8 @@ int gemm_tile_choice(int64_t rows, int64_t N, int cus);
 // epilogue `ep` on `cus` compute units (the values of MMF_TILE_* in mmf.h).
 enum GemmPlan { kPlan128x512 = 0, kPlan128x256Paired = 1, kPlan64x512 = 2, kPlan64x256 = 3, kPlan256x256 = 4 };
 int gemm_plan(int64_t rows, int K, int64_t N, Epilogue ep, int cus);
-// Estimated time of launch_gemm on a problem of few tiles: rounds of
-// workgroups over the CUs x the measured time of one tile's k loop alone.
-double gemm_alone_us(int64_t rows, int K, int64_t N, int cus);
+// Estimated microseconds of launch_gemm, without the outputs' share.
+double gemm_us(int64_t rows, int K, int64_t N, int cus);
 // Rows per launch of the MFMA kernel for K in-features and N out-features,
 // or 0 when the shape is beyond its 32-bit buffer offsets: the packed weights
 // must stay below 2^31 bytes, N at most 2^24, and a launch covers a slice of
@@ -139,11 +138,13 @@ inline int64_t gemm_row_slice(int64_t K, int64_t N) {
 struct SkinnyPlan {
   int fm = 0, fn = 0;  // 16-row and 16-column blocks of a workgroup's tile
   double cost = 0.0;
+  double rounds = 0.0;  // of tiles that take a whole compute unit (0: the others)
 };
 SkinnyPlan skinny_plan(int64_t M, int K, int64_t N, Epilogue ep, int cus);
-// Whether the automatic path runs the contraction of M rows on it rather than
-// on launch_gemm's tiles.
-bool skinny_takes(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus);
+// Whether it can contract M rows, and whether it is the better choice against
+// launch_gemm's tiles.
+bool skinny_fits(int64_t M, int K, int64_t N, Epilogue ep);
+bool skinny_beats_gemm(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus);
 hipError_t launch_skinny(const ContractArgs& a, bool tiled, hipStream_t stream);
 
 // Interleave the packed gate and up projections of a GLU, [K/16][L] each,

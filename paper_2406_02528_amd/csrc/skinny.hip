@@ -5,6 +5,8 @@
 
 namespace mmf {
 
+constexpr int64_t kSkinnyMaxRows = 40000;  // measured
+
 SkinnyPlan skinny_plan(int64_t M, int K, int64_t N, Epilogue ep, int cus) {
   // Estimated cost in KB through one compute unit: the rows and the packed
   // columns of a workgroup's tile plus what a workgroup costs beside them
@@ -32,33 +34,47 @@ SkinnyPlan skinny_plan(int64_t M, int K, int64_t N, Epilogue ep, int cus) {
       if (alone) rounds = (fn == 16 ? 1.45 : 1.25) * static_cast<double>(static_cast<int64_t>(rounds + 0.999999));
       if (rounds < 1.0) rounds = 1.0;
       const double cost = rounds * kb;
-      if (best.fm == 0 || cost < best.cost) best = {fm, fn, cost};
+      if (best.fm == 0 || cost < best.cost) best = {fm, fn, cost, alone ? rounds : 0.0};
     }
   }
   return best;
 }
 
-bool skinny_takes(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus) {
-  // 32-bit offsets: the packed weights, and a tile's rows of q
+// Estimated microseconds on the plan's tiles, fitted like gemm_us, without the
+// outputs' share: per KB through a compute unit, per round of whole-unit tiles
+// the sum of their partial tiles, which no other workgroup covers, and the
+// packed weights through HBM.  From rows of q a KB takes 1.2 to 1.35 times as
+// long as from tiled q.
+static double skinny_us(const SkinnyPlan& p, int K, int64_t N, bool tiled) {
+  const double us_per_kb = p.rounds == 0.0 ? (tiled ? 0.0212 : 0.0249)
+                           : p.fn < 16     ? (tiled ? 0.0162 : 0.0212)
+                                           : (tiled ? 0.0150 : 0.0202);
+  return 0.7 + us_per_kb * p.cost + 1.8 * p.rounds + 0.02e-6 * static_cast<double>(K) * static_cast<double>(N);
+}
+
+bool skinny_fits(int64_t M, int K, int64_t N, Epilogue ep) {
+  // 32-bit offsets: the packed weights
   if (M < 1 || N < 1 || static_cast<int64_t>(K / 16) * N * 4 >= (int64_t(1) << 31)) return false;
-  if (ep == Epilogue::kGluF32 && N % 32 != 0) return false;
-  if (ep == Epilogue::kAffineF32 && N % 4 != 0) return false;
+  return ep == Epilogue::kGluF32 ? N % 32 == 0 : ep == Epilogue::kAffineF32 ? N % 4 == 0 : true;
+}
+
+bool skinny_beats_gemm(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus) {
   if (M <= kDecodeMaxTokens) return true;
-  // Microseconds of a forward from x (act-quant included), fitted to 150
-  // shapes (K = 1024 to 13824, N = 1024 to 27648, M = 17 to 1536): this kernel
-  // within about 15 %, the tiled one by its tile's k loop when it runs alone.
-  // Its k loop slows down beyond K = 4096 when many tiles stream weights at
-  // once (33 instead of 24 us at K = 5120), hence the larger margin there.
-  // Measured on either side of the line (this kernel / tiled, us):
-  //   K = 2048, N = 6144:  M = 33 7.4 / 13.8, 128 9.0 / 14.2, 384 14.4 / 15.7, 640 19.8 / 17.1
-  //   K = 2048, N = 11264: M = 256 14.5 / 15.7, 320 19.2 / 16.3
-  //   K = 5632, N = 2048:  M = 64 8.1 / 25.9, 512 15.2 / 28.6, 1536 32.2 / 32.4
-  //   K = 5120, N = 15360: M = 128 19.5 / 33.7, 256 31.8 / 34.9, 512 58.1 / 41.7
-  //   K = 2992, N = 3998:  M = 64 8.1 / 39.0, 1024 27.7 / 57.2 (N % 4 != 0)
-  // From rows of q it takes up to 1.4 times as long as from tiled q.
-  const double mine = 4.5 + (tiled ? 0.0216 : 0.029) * skinny_plan(M, K, N, ep, cus).cost;
-  const double margin = !tiled ? 1.0 : K > 4096 ? 1.3 : 1.15;
-  return mine < margin * (3.0 + gemm_alone_us(M, K, N, cus));
+  // Beyond 16 rows: where it is estimated 5 % faster than the tiled kernel, up
+  // to the rows that were measured.  Over 2001 shapes of the fit and 1500 drawn
+  // ones (K = 16 to 16384, N = 16 to 125000) the chosen kernel takes 1.003 times
+  // the better one's time on average; 29 take this kernel and are 3 to 24 %
+  // slower for it, 41 the tiled one (3 to 62 %: row-layout q of few features).
+  // Forward calls from bf16 x on either side of the line, K-split / tiled, us:
+  //   K = 1024, N = 1024:  M = 1024 8.9 / 11.1, 2048 14.4 / 12.0
+  //   K = 2048, N = 2048:  M = 64 6.2 / 13.4, 1024 14.3 / 15.7, 1536 19.5 / 17.6
+  //   K = 2048, N = 6144:  M = 32 6.5 / 13.3, 384 14.7 / 15.6, 512 16.2 / 16.2, 768 22.1 / 20.7
+  //   K = 2048, N = 11264: M = 128 11.3 / 14.4, 256 15.6 / 15.6, 512 26.0 / 20.9
+  //   K = 5120, N = 2048:  M = 1024 21.2 / 29.4, 2048 30.7 / 31.7, 4096 55.4 / 45.5
+  //   K = 5120, N = 15360: M = 128 19.3 / 33.9, 256 27.4 / 35.3, 512 48.6 / 42.3
+  //   K = 2048, N = 2050:  M = 256 9.3 / 40.7, 768 13.0 / 15.9, 1536 20.1 / 18.1 (N % 4 != 0)
+  if (M > kSkinnyMaxRows) return false;
+  return skinny_us(skinny_plan(M, K, N, ep, cus), K, N, tiled) < 0.95 * gemm_us(M, K, N, cus);
 }
 
 hipError_t launch_skinny(const ContractArgs& a, bool tiled, hipStream_t stream) {

@@ -76,3 +76,26 @@ def test_calls_that_need_scratch_allocate_it():
             assert r["status"] == 0 and r["allocs"] == r["frees"] and kernels(r) == ["act_quant_kernel", "skinny_kernel"]
         failed = [r["status"] for r in record(_alloc_calls(M, K, fail_alloc=True))]
         assert failed == [5, 0, 5, 5]  # the second form's scratch is static
+
+
+# Both sides of the line between the K-split and the tiled kernel, from x and
+# from rows of q, as measured beside the rule in skinny.hip; the last ones are
+# tall and narrow (K-split re-reads the rows in every column strip).
+@pytest.mark.parametrize("K,N,split,tiled", [
+    (1024, 1024, [17, 1024], [2048, 16384]), (2048, 2048, [64, 1024], [1536, 4096]),
+    (2048, 6144, [32, 128, 384], [512, 640, 768]), (2048, 11264, [33, 128], [320, 512]),
+    (5120, 2048, [64, 1024], [4096]), (5120, 15360, [128, 256], [512, 1536]),
+    (2048, 2050, [256, 768], [1536]), (5120, 1024, [512], [8192]), (5120, 2050, [512], [16384]),
+    (13824, 3000, [512], [12000]), (1024, 64, [40000], [65536])])
+def test_few_rows_split_k_and_many_do_not(K, N, split, tiled):
+    calls = [call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, M, K, N, A, BIG, None) for M in split + tiled]
+    assert [kernels(r)[-1] for r in record(calls)] == ["skinny_kernel"] * len(split) + ["gemm_kernel"] * len(tiled)
+
+
+def test_decode_slices_give_way_to_the_k_split_kernel():
+    """17 to 64 rows that the tiled kernel would not get anyway: with scratch
+    (or from rows of q, which need none) never several decode launches."""
+    shapes = [(17, 32, 58752), (28, 144, 61216), (32, 7680, 11264), (64, 5120, 27648), (17, 16, 16)]
+    for r in record([call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, *s, A, BIG, None) for s in shapes] +
+                    [call("mmf_ternary_gemm_dequant", A, A, A, A, A, A, *s, None) for s in shapes]):
+        assert kernels(r)[-1] == "skinny_kernel"
