@@ -425,8 +425,8 @@ def test_mlgru_decode_step_fused_equals_in_place(mmf, B, d):
     """A decode step (T = 1) whose new state goes to its own array runs the
     recurrence and output gate in the output projection's prologue; with the
     state updated in place it runs the recurrence kernel and the plain
-    projection.  Same arithmetic: the same bits (B = 21 spans two 16-token
-    slices)."""
+    projection.  More than 16 sequences (B = 21) run both inside act-quant
+    either way.  Same arithmetic: the same bits."""
     rs = np.random.default_rng(7700 + B + d)
     bits, xf, gamma, W = workloads.random_case(rs, B, d, 3 * d)
     Wp, w_scales, _, _ = pack_fcg(mmf, W, True)

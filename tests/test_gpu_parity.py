@@ -217,14 +217,14 @@ def test_random_shapes(mmf, M):
 # once the wide tiles fill the CUs, run as two 128 x 256 workgroups per CU at
 # K <= 4096 beyond one round of wide tiles (the full-size workloads above
 # take both forms).  Ragged in every dimension (a partial last stage of K,
-# partial row and column tiles).  The automatic path sends 33-64 tokens to
-# the MFMA kernel at K <= 2048 and to decode launches of 16 tokens beyond.
+# partial row and column tiles).  On the automatic path the last two take the
+# K-split kernel, as the forced decode path runs them as several launches.
 @pytest.mark.parametrize("M,K,N", [(300, 1040, 2000),    # 64 x 256: 40 tiles
                                    (1000, 336, 6000),    # 64 x 512: 192 tiles
                                    (1100, 528, 8000),    # 128 x 512: 144 tiles, one round
                                    (3000, 400, 8200),    # 128 x 256 pairs: 816 tiles
-                                   (40, 2048, 1000),     # auto: MFMA kernel (64 x 256)
-                                   (57, 2064, 1000)])    # auto: four decode launches
+                                   (40, 2048, 1000),     # three decode launches when forced
+                                   (57, 2064, 1000)])    # four
 def test_gemm_tile_shapes(mmf, M, K, N):
     check_shape(mmf, np.random.default_rng(1100 + M + K), M, K, N, PATHS + ("auto",), tag="tiles")
 
@@ -467,7 +467,7 @@ def test_decode_up_to_16_tokens_per_launch(mmf, M, K, N, f32):
     need more registers than the fused kernel holds, from act-quant's q
     copied into LDS (16 x 7680 is the largest q region); 33 and 40 tokens as
     launches of 16, 16 and the rest on the forced decode path (the automatic
-    path sends more than 32 tokens at K <= 2048 to the MFMA kernel)."""
+    path sends them to the K-split kernel)."""
     rs = np.random.default_rng(M * 17 + K + N)
     bits, xf, g, W = workloads.random_case(rs, M, K, N)
     x_form = xf if f32 else bits

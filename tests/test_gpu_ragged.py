@@ -50,12 +50,16 @@ def test_odd_widths_equal_the_widened_matrix(mmf, M, K, N, plan):  # noqa: F811
         mmf.mmf_set_path(prev)
 
 
-# dY on 64 x 256 tiles (few tiles; a partial last round) and on 128 x 512 tiles
-# (a full round), ragged in tokens and input features, N odd and N % 8 != 0
-# (dO rows on any 2 bytes, rows shorter than a chunk).
-@pytest.mark.parametrize("M,K,N,f32_x,with_gamma", [(65, 272, 9, False, True), (130, 1040, 127, True, True),
-                                                    (1937, 528, 77, False, False), (2, 16, 3, True, False),
-                                                    (16300, 1008, 40, False, True)])
+# dY on 64 x 256 and on 128 x 512 tiles (the tile of each on 256 compute units,
+# checked without a GPU by test_routes.py), ragged in tokens and input
+# features, N odd and N % 8 != 0 (dO rows on any 2 bytes, rows shorter than a
+# chunk).
+DY_TILES = {(65, 272, 9, False, True): (64, 256), (130, 1040, 127, True, True): (64, 256),
+            (1937, 528, 77, False, False): (64, 256), (2, 16, 3, True, False): (64, 256),
+            (16300, 1008, 40, False, True): (128, 512), (16300, 1008, 41, True, False): (128, 512)}
+
+
+@pytest.mark.parametrize("M,K,N,f32_x,with_gamma", DY_TILES)
 def test_dy_tiles(mmf, M, K, N, f32_x, with_gamma):  # noqa: F811
     print(f"dY M={M} K={K} N={N}", flush=True)
     run_bwd(mmf, M, K, N, f32_x, with_gamma, seed=11)

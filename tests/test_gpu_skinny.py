@@ -46,20 +46,37 @@ def weights(mmf, N, K, seed):
     return mmf.ternarize(torch.randn(N, K, generator=g, device="cuda") * 0.02)
 
 
-# Row blocks of one to four 16-row fragments and several row blocks, their last
-# one partly filled; column strips of 1, 2, 4 and 8 blocks with ragged ends, N
-# odd and N % 4 == 2; K with a last step of 16, 32 and 48 features, fewer steps
-# than waves, and more than two steps per wave.
-SHAPES = [(17, 16, 100), (17, 1040, 1000), (31, 2064, 6000), (33, 2096, 2044), (45, 5632, 2048), (47, 2080, 11266),
-          (64, 528, 301), (65, 1024, 4096), (70, 4112, 260), (100, 2048, 11264), (129, 1072, 3001), (257, 2048, 1000),
-          (400, 112, 48), (1, 16400, 96), (5, 13824, 324), (16, 13824, 5120), (33, 1024, 5)]
+# The tile each shape runs on (256 compute units), as row blocks x column blocks
+# / steps in flight, or the kernel that takes it instead; test_routes.py checks
+# them without a GPU.  Together: every tile form, several row blocks with the
+# last one partly filled or without whole blocks, ragged ends of the column
+# strips, N odd and N % 4 == 2; K with a last step of 16, 32 and 48 features,
+# fewer steps than waves, and more than two steps per wave.
+FORWARD = {
+    (17, 16, 100): "1x1/2", (17, 1040, 1000): "1x1/4", (31, 2064, 6000): "1x4/4", (33, 2096, 2044): "1x2/4",
+    (45, 5632, 2048): "1x2/4", (47, 2080, 11266): "1x8/4", (64, 528, 301): "1x1/2", (65, 1024, 4096): "2x4/2",
+    (70, 4112, 260): "1x1/4", (100, 2048, 11264): "2x8/2", (129, 1072, 3001): "2x4/4", (257, 2048, 1000): "1x4/4",
+    (400, 112, 48): "1x1/2", (1, 16400, 96): "decode", (5, 13824, 324): "decode", (16, 13824, 5120): "1x2/4",
+    (33, 1024, 5): "1x1/2",
+    # the 64 x 256 tile (two column halves, four shares of K), ragged in each dimension
+    (100, 2064, 27000): "4x16/2", (127, 1040, 27001): "4x16/2", (250, 4112, 15300): "4x16/2",
+    # two and three row blocks (three: a last round of partial sums half
+    # filled), tiles of a whole compute unit, at long K and ragged
+    (39, 2096, 3298): "2x2/4", (97, 1616, 4589): "1x8/4", (153, 1040, 1872): "3x2/4", (150, 1040, 1873): "3x2/4",
+    (128, 13824, 5120): "3x4/2", (128, 5120, 5120): "3x4/2", (93, 1040, 6864): "3x4/2", (115, 1040, 4649): "3x4/2",
+    (130, 1664, 10380): "3x8/2", (84, 1040, 15358): "3x8/2", (112, 928, 13572): "4x8/2", (100, 1040, 15358): "4x8/2",
+    (128, 5120, 15360): "4x8/2"}
+RAW = {(17, 16, 100): "1x1/2", (45, 2096, 2044): "1x2/4", (100, 1040, 6001): "2x8/2", (130, 512, 8192): "2x8/2",
+       (81, 1040, 6737): "3x4/2", (100, 144, 10865): "3x8/2", (50, 1040, 26221): "4x8/2", (437, 176, 1300): "3x4/2"}
+GLU = {(17, 16, 16): "1x2/2", (33, 1040, 2832): "1x4/4", (45, 2048, 5632): "1x8/4", (200, 2064, 528): "1x4/4",
+       (128, 5120, 1744): "2x4/4", (120, 1040, 13824): "tiled", (37, 1200, 1568): "2x2/4", (357, 2064, 720): "2x4/4",
+       (183, 1184, 3888): "3x8/2", (196, 1120, 3744): "4x8/2", (130, 1312, 10272): "4x16/2", (308, 16, 816): "3x4/2"}
+GATES = {(17, 64, 16): "1x1/2", (33, 1040, 1040): "2x2/4", (45, 2048, 2048): "2x4/4", (300, 528, 272): "1x4/2",
+         (153, 1040, 624): "3x2/4", (128, 5120, 1712): "3x4/2", (325, 1264, 1536): "3x8/2", (298, 2800, 1984): "4x8/2",
+         (74, 1392, 8608): "4x16/2"}
 
 
-# the 64 x 256 tile (two column halves, four shares of K), ragged in each dimension
-SHAPES += [(100, 2064, 27000), (127, 1040, 27001), (250, 4112, 15300)]
-
-
-@pytest.mark.parametrize("M,K,N", SHAPES)
+@pytest.mark.parametrize("M,K,N", FORWARD)
 @pytest.mark.parametrize("f32", [False, True])
 def test_forward_equals_the_gemm_path(mmf, M, K, N, f32):
     print(f"forward M={M} K={K} N={N} f32={f32}", flush=True)
@@ -81,7 +98,7 @@ def test_forward_equals_the_gemm_path(mmf, M, K, N, f32):
     assert torch.equal(mmf.bitlinear(x, gamma, Wp, ws).cpu(), b)
 
 
-@pytest.mark.parametrize("M,K,N", [(17, 16, 100), (45, 2096, 2044), (100, 1040, 6001), (130, 512, 8192)])
+@pytest.mark.parametrize("M,K,N", RAW)
 def test_integer_sums_from_rows_of_q(mmf, M, K, N):
     print(f"raw M={M} K={K} N={N}", flush=True)
     rs = np.random.default_rng(3)
@@ -95,7 +112,7 @@ def test_integer_sums_from_rows_of_q(mmf, M, K, N):
     assert torch.equal(acc.cpu().to(torch.int64), q.to(torch.int64) @ t.t())
 
 
-@pytest.mark.parametrize("M,K,L", [(17, 16, 16), (33, 1040, 2832), (45, 2048, 5632), (200, 2064, 528), (128, 5120, 1744), (120, 1040, 13824)])
+@pytest.mark.parametrize("M,K,L", GLU)
 def test_glu_equals_the_gemm_path(mmf, M, K, L):
     print(f"glu M={M} K={K} L={L}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(5)
@@ -112,7 +129,7 @@ def test_glu_equals_the_gemm_path(mmf, M, K, L):
     assert same(a, b)
 
 
-@pytest.mark.parametrize("M,K,d", [(17, 64, 16), (33, 1040, 1040), (45, 2048, 2048), (300, 528, 272)])
+@pytest.mark.parametrize("M,K,d", GATES)
 @pytest.mark.parametrize("full", [False, True])
 def test_gates_equal_the_gemm_path(mmf, M, K, d, full):
     print(f"gates M={M} K={K} d={d} full={full}", flush=True)

@@ -1,7 +1,11 @@
 """The kernels that calls of the C ABI launch (host side only: tests/record.py
 records the launches of the built library on 256 compute units)."""
+import re
+
 import pytest
 
+import test_gpu_ragged
+import test_gpu_skinny
 from record import AUTO, GEMM, GEMV, call, kernels, record  # noqa: F401
 
 A = 0x100000000  # made-up 256-byte aligned device address, never dereferenced
@@ -99,3 +103,43 @@ def test_decode_slices_give_way_to_the_k_split_kernel():
     for r in record([call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, *s, A, BIG, None) for s in shapes] +
                     [call("mmf_ternary_gemm_dequant", A, A, A, A, A, A, *s, None) for s in shapes]):
         assert kernels(r)[-1] == "skinny_kernel"
+
+
+def _form(launch):
+    """A skinny_kernel's row blocks x column blocks / steps in flight."""
+    m = re.match(r"skinny_kernel<(\d+), (\d+), (\d+), (\d+), (\d+), ", launch["kernel"])
+    return f"{m[1]}x{int(m[2]) * int(m[3]) * int(m[4])}/{m[5]}" if m else \
+        {"gemm_kernel": "tiled", "decode_kernel": "decode"}[launch["kernel"].split("<")[0]]
+
+
+@pytest.mark.parametrize("name", ["FORWARD", "RAW", "GLU", "GATES"])
+def test_gpu_shapes_take_the_tiles_they_name(name):
+    """The K-split tile forms that test_gpu_skinny.py names beside its shapes."""
+    shapes = getattr(test_gpu_skinny, name)
+    make = {"FORWARD": lambda M, K, N: call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, M, K, N, A, BIG, None),
+            "RAW": lambda M, K, N: call("mmf_ternary_gemm_i32", A, A, A, M, K, N, None),
+            "GLU": lambda M, K, L: call("mmf_glu_fwd_ws", A, 0, A, A, A, A, M, K, L, A, BIG, None),
+            "GATES": lambda M, K, d: call("mmf_mlgru_proj", A, 0, A, A, A, A, A, A, M, K, d, A, BIG, None)}[name]
+    out = record([make(*s) for s in shapes])
+    assert {s: _form(r["launches"][-1]) for s, r in zip(shapes, out)} == shapes
+
+
+def test_gpu_dy_shapes_take_the_tiles_they_name():
+    want = test_gpu_ragged.DY_TILES
+    for (tile, r) in zip(want.values(), record([bwd(*s[:3]) for s in want])):
+        assert [k["kernel"] for k in r["launches"] if k["kernel"].startswith("dy_kernel")] == \
+            ["dy_kernel<unsigned short, DyTile<%d, %d> >" % tile]
+
+
+# One token per sequence through the mixer: where the recurrence runs.  Inside
+# the output projection's decode launch where that takes the rows and the new
+# state is an array of its own; with the state in place as its own launch;
+# otherwise inside act-quant.
+@pytest.mark.parametrize("B,in_place,want", [
+    (1, False, ["decode_kernel", "decode_kernel"]), (16, False, ["decode_kernel", "act_quant_kernel", "skinny_kernel"]),
+    (4, True, ["decode_kernel", "mlgru_apply_kernel", "decode_kernel"]),
+    (17, False, ["act_quant_kernel", "skinny_kernel"] * 2), (17, True, ["act_quant_kernel", "skinny_kernel"] * 2)])
+def test_decode_step_routes(B, in_place, want):
+    h = A if in_place else 2 * A
+    r = record([call("mmf_mlgru_fwd", A, 0, A, A, A, A, A, A, h, A, A, A, A, A, B, 1, 2048, A, BIG, None)])[0]
+    assert r["status"] == 0 and kernels(r) == want
