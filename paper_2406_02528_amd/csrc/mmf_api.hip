@@ -802,9 +802,12 @@ int mmf_mlgru_fwd(const void* x, int x_is_f32, const float* gamma, const uint32_
       }
       return MMF_OK;
     }
-    // More sequences, or the state updated in place: the step and the output
-    // gate in the activation quantisation, whose rows each belong to one
-    // workgroup (no o' round trip, one launch less; the same bits).
+    // Sequences whose output projection does not run as fused decode launches,
+    // the state in place or not: the step and the output gate in the activation
+    // quantisation, whose rows each belong to one workgroup (no o' round trip,
+    // one launch less; the same bits).  Fewer sequences with the state in place
+    // take the recurrence kernel below: each workgroup of the prologue above
+    // reads the state that one of them stores.
     if (T == 1 && route != Route::kFusedDecode && mmf::act_quant_mlgru_fits(static_cast<int>(d))) {
       const FwdScratch f = fwd_scratch(M, d);
       char* const qs = scratch + s.q_off;
