@@ -417,17 +417,20 @@ int mmf_set_path(int path);
 
 /*
  * The workgroup tile of the tiled prefill (MFMA GEMM) contraction for an
- * M x K x N problem on `cus` compute units, as the library plans it for its launches
- * (host only: no device call, nothing enqueued; for problems split into row
+ * M x K x N problem on `cus` compute units, as the library plans it for its
+ * launches of that kernel (host only: no device call, nothing enqueued; for problems split into row
  * slices by the 32-bit offset limit, the first slice's plan).  For callers
  * sizing their own work and for tests that must know which kernel form a
  * shape exercises.  `epilogue` is one of MMF_EPILOGUE_*; for the GLU, N is
- * the interleaved width 2 L (a multiple of 32).  Returns one of MMF_TILE_*:
+ * the interleaved width 2 L (a multiple of 32); MMF_EPILOGUE_AFFINE is that of
+ * mmf_mlgru_proj's gates, while a bias alone (mmf_bitlinear_fwd_bias, the
+ * training forward, the mixer's output projection) runs on the tiles of
+ * MMF_EPILOGUE_DEQUANT.  Returns one of MMF_TILE_*:
  * 128 x 512 tiles with one 8-wave workgroup per CU; the same area as two
  * 128 x 256 workgroups of 4 waves per CU (K <= 4096, not the affine
  * epilogue, more than one round of wide tiles or most of one at K <= 2048);
- * 64 x 512 or 64 x 256 tiles for problems with few wide tiles; 256 x 256
- * when N % 4 != 0.  Errors as negative status: -MMF_ERR_SHAPE for a shape the
+ * 64 x 512 or 64 x 256 tiles for problems with few wide tiles; 256 x 256 for
+ * up to 256 rows when N % 4 != 0.  Errors as negative status: -MMF_ERR_SHAPE for a shape the
  * contraction rejects or cus < 1, -MMF_ERR_ARG for an unknown epilogue.
  */
 #define MMF_EPILOGUE_DEQUANT 0

@@ -61,8 +61,6 @@
 namespace mmf {
 namespace {
 
-// BX4: B rows are copied 16 bytes per lane (one word row per instruction),
-// which needs N % 4 == 0 for aligned rows; otherwise 4 bytes per lane.
 // The lane's index in its wave, computed afresh and hidden from the
 // optimiser: values derived from it after a k loop that takes every register
 // are then recomputed there instead of being kept (spilled) across the loop.
@@ -72,6 +70,8 @@ __device__ __forceinline__ int fresh_lane_id() {
   return l;
 }
 
+// BX4: B rows are copied 16 bytes per lane (one word row per instruction),
+// from any dword (N % 4 != 0: the RAG stores below); otherwise 4 bytes per lane.
 template <int BM, int BN, int WM, int WN, int BK, int S, bool BX4>
 struct Tiling {
   static constexpr int kWavesM = BM / WM, kWavesN = BN / WN;
@@ -442,8 +442,8 @@ __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(
   // Plain outputs (dequantised or raw int32) leave through LDS as whole row
   // segments (below); the GLU and affine epilogues, whose output rows are
   // half as wide or whose launches are a single round, measured no faster
-  // that way and keep direct 16-byte stores, and N % 4 != 0 takes
-  // per-element stores.
+  // that way and keep direct 16-byte stores, and the 256 x 256 tile of few rows
+  // at N % 4 != 0 takes per-element stores.
   constexpr bool kStaged = BX4 && (EP == Epilogue::kDequantF32 || EP == Epilogue::kRawI32);
   static_assert(!RAG || kStaged, "ragged rows leave through the staged stores");
   static_assert(!BIAS || (kStaged && !RAG && EP == Epilogue::kDequantF32), "the bias is added at the staged stores");

@@ -4,6 +4,7 @@ import re
 
 import pytest
 
+import paper_2406_02528_amd as mmf
 import test_gpu_ragged
 import test_gpu_skinny
 from record import AUTO, GEMM, GEMV, call, kernels, record  # noqa: F401
@@ -129,6 +130,29 @@ def test_gpu_dy_shapes_take_the_tiles_they_name():
     for (tile, r) in zip(want.values(), record([bwd(*s[:3]) for s in want])):
         assert [k["kernel"] for k in r["launches"] if k["kernel"].startswith("dy_kernel")] == \
             ["dy_kernel<unsigned short, DyTile<%d, %d> >" % tile]
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (256, 1024, 1002), (257, 1024, 1002), (1937, 2288, 3998), (8192, 2048, 11266), (40, 512, 2304), (300, 1040, 2304),
+    (2048, 2048, 6144), (2048, 2048, 1920), (4096, 1024, 8256), (8192, 2048, 11328), (1024, 5120, 15360)])
+def test_tile_plan_names_the_tile_that_is_launched(M, K, N):
+    """mmf_prefill_tile_plan against the launches of the tiled kernel, for every
+    epilogue; a bias alone runs on the dequantising epilogue's tiles."""
+    ws = (M, K, N, A, BIG, None)
+    forms = {mmf.MMF_EPILOGUE_DEQUANT: [call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, *ws, path=GEMM)],
+             mmf.MMF_EPILOGUE_RAW_I32: [call("mmf_ternary_gemm_i32", A, A, A, M, K, N, None, path=GEMM)]}
+    if N % 4 == 0:
+        forms[mmf.MMF_EPILOGUE_DEQUANT].append(call("mmf_bitlinear_fwd_bias", A, 0, A, A, A, A, A, M, K, N, None, path=GEMM))
+    if N % 32 == 0:
+        forms[mmf.MMF_EPILOGUE_GLU] = [call("mmf_glu_fwd_ws", A, 0, A, A, A, A, M, K, N // 2, A, BIG, None, path=GEMM)]
+    if N % 48 == 0:
+        forms[mmf.MMF_EPILOGUE_AFFINE] = [
+            call("mmf_mlgru_proj", A, 0, A, A, A, A, A, A, M, K, N // 3, A, BIG, None, path=GEMM)]
+    for ep, calls in forms.items():
+        plan = mmf.mmf_prefill_tile_plan(M, K, N, ep).removesuffix("_paired")
+        for r in record(calls):
+            assert r["status"] == 0
+            assert re.match(r"gemm_kernel<(\d+), (\d+), ", r["launches"][-1]["kernel"]).groups() == tuple(plan.split("x"))
 
 
 # One token per sequence through the mixer: where the recurrence runs.  Inside
