@@ -207,12 +207,13 @@ template <> struct X4<float> {
 // dg_part [ceil(M/BM)][K] or null, db_part [ceil(M/BM)][N] or null.
 //
 // db duty: the column tiles of a row tile read the same dO rows, so each
-// 64-column stage of dO is summed over the row tile's 128 rows by one of them
+// 64-column stage of dO is summed over the row tile's BM rows by one of them
 // (stage kt by column tile kt % ntn) while the stage is in LDS: wave w sums
-// the 8 columns of chunk w, lane (row group g8 = lane / 8, column lane % 8)
-// the 16 rows g8 + 8 i in fp64 (bf16 values are exact in fp64), then the 8
-// row groups are added in order through the wave's own LDS scratch and the
-// sum goes to db_part[tm][n].
+// the 8 columns of each of its chunks w, w + kWaves, ... (one chunk of 8 waves,
+// two of 4), lane (row group g8 = lane / 8, column lane % 8) the BM / 8 rows
+// g8 + 8 i in fp64 (bf16 values are exact in fp64), then the 8 row groups are
+// added in order through the wave's own LDS scratch and the sum goes to
+// db_part[tm][n].
 template <typename XT, typename T>
 __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(2))) void dy_kernel(
     const uint16_t* __restrict__ dO, const uint32_t* __restrict__ Wn, const float* __restrict__ w_scale,
