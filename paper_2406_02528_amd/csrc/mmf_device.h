@@ -255,6 +255,31 @@ __device__ __forceinline__ ColAffine load_col_affine(const Affine& a, const floa
   return c;
 }
 
+// F consecutive packed words (one 4-, 8- or 16-byte buffer load).
+template <int F>
+struct Words {
+  uint32_t w[F];
+};
+template <int F>
+__device__ __forceinline__ Words<F> load_words(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff) {
+  Words<F> r;
+  if constexpr (F == 1) {
+    r.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
+  } else if constexpr (F == 2) {
+    const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
+    r.w[0] = v.x;
+    r.w[1] = v.y;
+  } else {
+    static_assert(F == 4, "one, two or four words");
+    const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
+    r.w[0] = v.x;
+    r.w[1] = v.y;
+    r.w[2] = v.z;
+    r.w[3] = v.w;
+  }
+  return r;
+}
+
 // Four consecutive columns n .. n + 3 (n % 4 == 0, seg % 16 == 0: one segment).
 typedef float v4f __attribute__((ext_vector_type(4)));
 struct ColAffine4 {

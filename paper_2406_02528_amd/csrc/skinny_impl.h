@@ -73,30 +73,6 @@ constexpr int rows_per_round(int fm, int fn) {
 // the second workgroup on a compute unit).
 constexpr bool skinny_deep(int fm, int fn) { return fn <= 2 || fm == 1 || (fm == 2 && fn == 4); }
 
-template <int F>
-struct Words {
-  uint32_t w[F];
-};
-template <int F>
-__device__ __forceinline__ Words<F> load_words(__amdgpu_buffer_rsrc_t rsrc, uint32_t voff, uint32_t soff) {
-  Words<F> r;
-  if constexpr (F == 1) {
-    r.w[0] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, voff, soff, 0);
-  } else if constexpr (F == 2) {
-    const uint2 v = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
-    r.w[0] = v.x;
-    r.w[1] = v.y;
-  } else {
-    static_assert(F == 4, "one, two or four words");
-    const uint4 v = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, soff, 0));
-    r.w[0] = v.x;
-    r.w[1] = v.y;
-    r.w[2] = v.z;
-    r.w[3] = v.w;
-  }
-  return r;
-}
-
 // VEC: N % 4 == 0.  Otherwise the word rows start on any dword (buffer loads
 // need dword alignment only and are range-checked dword by dword; columns past
 // N read the next word row or zero and are dropped), and the outputs that
