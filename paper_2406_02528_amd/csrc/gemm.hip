@@ -666,14 +666,19 @@ constexpr int64_t kRaggedMinRows = 257;
 // where the tile has the CU to itself), the packed weights through HBM, and
 // the launch; fitted to 2001 shapes (K = 512 to 13824, N = 64 to 27648, M = 17
 // to 16384; within 20 %).  What the K-split kernel shares (act-quant, the
-// outputs) is left out.
+// outputs) is left out.  Weights that no cache holds yet, as those of a model's
+// next layer, hold up every stage of the first round (2048 x 2048 x 2048 from x
+// 19.2 us with the weights in the last-level cache, 21.1 without; the K-split
+// kernel, with more steps in flight, 21.1 and 21.5): 0.85 ns per feature beyond
+// the first 800, fitted to 737 shapes with cold weights.
 double gemm_us(int64_t rows, int K, int64_t N, int cus) {
   struct Shape { int64_t bm, bn; double us, us_per_k; };
   constexpr Shape kShapes[] = {
       {128, 512, 0.4, 0.0075}, {64, 512, 0.1, 0.0050}, {64, 256, 0.0, 0.0037}, {256, 256, 11.0, 0.0087}};
   const Shape& s = kShapes[N % 4 != 0 && rows < kRaggedMinRows ? 3 : gemm_tile_choice(rows, N, cus)];
   const int64_t tiles = ((rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), c = cus > 0 ? cus : 256;
-  return 2.3 + static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K) +
+  const double cold = K > 800 ? 0.00085 * (K - 800) : 0.0;
+  return 2.3 + cold + static_cast<double>((tiles + c - 1) / c) * (s.us + s.us_per_k * K) +
          0.055e-6 * static_cast<double>(K) * static_cast<double>(N);
 }
 

@@ -61,18 +61,19 @@ bool skinny_fits(int64_t M, int K, int64_t N, Epilogue ep) {
 bool skinny_beats_gemm(int64_t M, int K, int64_t N, Epilogue ep, bool tiled, int cus) {
   if (M <= kDecodeMaxTokens) return true;
   // Beyond 16 rows: where it is estimated 5 % faster than the tiled kernel, up
-  // to the rows that were measured.  Over 2001 shapes of the fit and 1500 drawn
-  // ones (K = 16 to 16384, N = 16 to 125000) the chosen kernel takes 1.003 times
-  // the better one's time on average; 29 take this kernel and are 3 to 24 %
-  // slower for it, 41 the tiled one (3 to 62 %: row-layout q of few features).
+  // to the rows that were measured.  Over 610 shapes of 65 to 36000 rows (K =
+  // 64 to 13824, N = 64 to 27648), with weights that no cache holds, the chosen
+  // kernel takes 1.003 times the better one's time on average (rows of q:
+  // 1.005); 7 run this kernel, 11 the tiled one, and are 3 to 18 % slower for
+  // it.  With weights and outputs in the last-level cache: 1.003.
   // Forward calls from bf16 x on either side of the line, K-split / tiled, us:
-  //   K = 1024, N = 1024:  M = 1024 8.9 / 11.1, 2048 14.4 / 12.0
-  //   K = 2048, N = 2048:  M = 64 6.2 / 13.4, 1024 14.3 / 15.7, 1536 19.5 / 17.6
-  //   K = 2048, N = 6144:  M = 32 6.5 / 13.3, 384 14.7 / 15.6, 512 16.2 / 16.2, 768 22.1 / 20.7
-  //   K = 2048, N = 11264: M = 128 11.3 / 14.4, 256 15.6 / 15.6, 512 26.0 / 20.9
-  //   K = 5120, N = 2048:  M = 1024 21.2 / 29.4, 2048 30.7 / 31.7, 4096 55.4 / 45.5
-  //   K = 5120, N = 15360: M = 128 19.3 / 33.9, 256 27.4 / 35.3, 512 48.6 / 42.3
-  //   K = 2048, N = 2050:  M = 256 9.3 / 40.7, 768 13.0 / 15.9, 1536 20.1 / 18.1 (N % 4 != 0)
+  //   K = 1024, N = 1024:  M = 1024 9.2 / 10.6, 1536 11.7 / 11.5, 2048 14.0 / 11.8
+  //   K = 2048, N = 2048:  M = 64 6.7 / 16.4, 1024 14.7 / 18.3, 2048 21.5 / 21.1, 3072 30.4 / 26.8
+  //   K = 2048, N = 6144:  M = 32 7.2 / 16.6, 384 15.7 / 18.7, 640 17.9 / 19.6, 768 25.6 / 22.6
+  //   K = 2048, N = 11264: M = 128 12.4 / 18.2, 320 17.2 / 19.3, 384 21.2 / 22.1, 512 28.2 / 22.3
+  //   K = 5120, N = 2048:  M = 1024 22.5 / 35.8, 2048 31.7 / 38.1, 3072 60.3 / 46.4
+  //   K = 5120, N = 15360: M = 128 19.3 / 33.7, 256 27.6 / 35.4, 320 36.6 / 40.9, 384 45.8 / 40.9
+  //   K = 2048, N = 2050:  M = 256 9.7 / 43.2, 768 13.7 / 18.5, 2048 27.1 / 24.4 (N % 4 != 0)
   if (M > kSkinnyMaxRows) return false;
   return skinny_us(skinny_plan(M, K, N, ep, cus), K, N, tiled) < 0.95 * gemm_us(M, K, N, cus);
 }

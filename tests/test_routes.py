@@ -87,11 +87,11 @@ def test_calls_that_need_scratch_allocate_it():
 # from rows of q, as measured beside the rule in skinny.hip; the last ones are
 # tall and narrow (K-split re-reads the rows in every column strip).
 @pytest.mark.parametrize("K,N,split,tiled", [
-    (1024, 1024, [17, 1024], [2048, 16384]), (2048, 2048, [64, 1024], [1536, 4096]),
-    (2048, 6144, [32, 128, 384], [512, 640, 768]), (2048, 11264, [33, 128], [320, 512]),
-    (5120, 2048, [64, 1024], [4096]), (5120, 15360, [128, 256], [512, 1536]),
-    (2048, 2050, [256, 768], [1536]), (5120, 1024, [512], [8192]), (5120, 2050, [512], [16384]),
-    (13824, 3000, [512], [12000]), (1024, 64, [40000], [65536])])
+    (1024, 1024, [17, 1024], [2048, 16384]), (2048, 2048, [64, 1024, 2048], [3072, 4096]),
+    (2048, 6144, [32, 128, 384, 640], [768, 1024]), (2048, 11264, [33, 128, 320], [512]),
+    (5120, 2048, [64, 1024, 2048], [3072, 4096]), (5120, 15360, [128, 256], [384, 512, 1536]),
+    (2048, 2050, [256, 768], [2048]), (5120, 1024, [512], [8192]), (5120, 2050, [512], [16384]),
+    (13824, 3000, [512], [12000]), (13824, 11264, [256, 384], [512]), (1024, 64, [40000], [65536])])
 def test_few_rows_split_k_and_many_do_not(K, N, split, tiled):
     calls = [call("mmf_bitlinear_fwd_ws", A, 0, A, A, A, A, M, K, N, A, BIG, None) for M in split + tiled]
     assert [kernels(r)[-1] for r in record(calls)] == ["skinny_kernel"] * len(split) + ["gemm_kernel"] * len(tiled)
