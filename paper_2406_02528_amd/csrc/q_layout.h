@@ -23,8 +23,8 @@ namespace mmf {
 // row in a last step of less than 64).  Byte offset of row r of a block of mr
 // rows, feature k, from the block:
 MMF_HOST_DEVICE inline int tiled_q_piece(int r, int mr, int k, int K) {
-  const int s = k / 64, piece = K - 64 * s < 64 ? K - 64 * s : 64;
-  return 64 * s * mr + r * piece + k % 64;
+  const int at = k & 63, rest = K - (k - at), piece = rest < 64 ? rest : 64;
+  return (k - at) * mr + r * piece + at;
 }
 
 // The scalar offset base + s step of 16-row block fm at k64 step s, from the
@@ -42,8 +42,9 @@ MMF_HOST_DEVICE inline QBlock q_block(int rows, int fm, int K, bool tiled) {
 // The lane offset of bytes 16 g .. 16 g + 15 of a step of row r in its block;
 // `last`: of the last step, whose tiled pieces may be shorter.
 MMF_HOST_DEVICE inline uint32_t q_lane(int r, int g, int K, bool tiled, bool last) {
-  const int pitch = !tiled ? K : last && K % 64 != 0 ? K % 64 : 64;
-  return static_cast<uint32_t>(r) * static_cast<uint32_t>(pitch) + 16u * static_cast<uint32_t>(g);
+  const uint32_t rest = static_cast<uint32_t>(K) & 63u;  // no branch: a kernel starts with these
+  const uint32_t piece = last && rest != 0 ? rest : 64u, pitch = tiled ? piece : static_cast<uint32_t>(K);
+  return static_cast<uint32_t>(r) * pitch + 16u * static_cast<uint32_t>(g);
 }
 
 // 16-byte vector v of a row of MLGRU gates (f, c and g, K floats each, side by
