@@ -351,7 +351,7 @@ hipError_t launch_mlgru_w(const Args& a, int vpl, hipStream_t stream) {
 // Waves per row: one while a lane holds at most 4 vectors of the row, else 2,
 // 4, 8 or 16, so that rows up to 64 x 16 x 8 vectors stay in registers (bf16
 // K <= 65536, fp32 K <= 32768; read three times from memory instead, a row of
-// 13824 fp32 took 16.3 us and 4096 of them 158 us, now 4.0 and 55 us).  With
+// 13824 fp32 took 16.3 us and 4096 of them 158 us, now 3.7 and 49 us).  With
 // so few rows that most of the chip idles anyway, up to 4 waves share what one
 // or two would hold (45 rows of 2048 bf16: 2.7 -> 2.5 us; at 256 rows it
 // measured slower, 2.3 -> 2.6 us at K = 1024, as did 16 waves per row).
