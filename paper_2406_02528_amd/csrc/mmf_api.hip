@@ -377,9 +377,9 @@ BwdScratch bwd_scratch(int64_t M, int64_t K, int64_t N) {
   s.dop_off = round_up(static_cast<size_t>(mmf::bwd_nmajor_words(N, K)) * 4, kScratchAlign);
   const size_t dop = s.Np != N ? static_cast<size_t>(M) * static_cast<size_t>(s.Np) * 2 : 0;
   s.spart_off = s.dop_off + round_up(dop, kScratchAlign);
-  // The dY partials of the smallest tile whatever the plan: the size then
-  // never falls as M grows, so the workspace of the largest batch serves
-  // every smaller one.
+  // The dY partials of the smallest tile whatever the plan: their share then
+  // never falls as M grows, so the workspace of the largest batch also serves
+  // a smaller one on that tile (what dW's parts take varies with its plan).
   const int64_t row_tiles = (M + mmf::kDyMinRows - 1) / mmf::kDyMinRows;
   const int64_t col_tiles = (K + mmf::kDyMinCols - 1) / mmf::kDyMinCols;
   s.dgpart_off = s.spart_off + round_up(sizeof(double) * static_cast<size_t>(col_tiles * M), kScratchAlign);
